@@ -11,9 +11,9 @@
 // B = (1 - S)/2 in {0,1}:
 //   G^r = S S^T = Ltau - 2 (n_x + n_y) + 4 (B B^T)_xy,  n_x = sum_tau B_x,tau
 //   Q^ab = S^aT S^b = L^2 - 2 (m^a_tau + m^b_tau') + 4 (B^aT B^b)_tau,tau'
-// so the GEMMs run on {0,1} int8 operands (cheap to unpack from bits) with
-// int32 accumulation on v_mfma_i32_32x32x32_i8, exactly.  Per pair a < b the
-// epilogues reduce, in int64,
+// so G runs on {0,1} operands (cheap to unpack from bits) and Q on +-1 ones,
+// both exact on the matrix cores.  Per pair a < b the epilogues reduce, in
+// int64,
 //   D_x[d] = sum_{(x1-y1) mod L = d} G^a_xy G^b_xy (and D_y in x2 - y2),
 //   trQ = sum_tau Q_tau,tau,  sum Q^2,  sum Q^4,
 // without storing G or Q.
@@ -26,11 +26,10 @@
 //    G (upper triangle of tile pairs), all replicas at once, bucket sums in
 //    LDS, flushed once per configuration; for Ltau <= 8192 on fp4 MFMAs
 //    (v_mfma_scale_f32_32x32x64_f8f6f4: {0, 0.5} operands, exact in fp32).
-// 3. k_overlap_mfma: every wave alone (no LDS, no barrier) on 64x64 tiles of
-//    a group of 2 pairs at once that share a replica on one side (one launch
-//    per group, two waves per SIMD), operands unpacked in registers, the rank-one corrections folded into one more
-//    K step so the accumulator is Q; per-lane int64 sums flushed once per
-//    configuration by each of the wave teams that share it.
+// 3. k_overlap_mfma: panels of rows tau of one configuration, every pair in
+//    turn, on fp4 MFMAs with +-1 operands (Q itself in the accumulators), the
+//    row operands expanded once per panel into LDS, the column operands built
+//    in registers, Q^4 summed in 64-bit integers.
 // The plain per-sample form (k_*_plain) computes one matrix element per
 // thread with an int32 multiply-accumulate loop over unpacked spins, one
 // launch per configuration: the reference point for the batched form.
@@ -161,6 +160,11 @@ __global__ void __launch_bounds__(256) k_transpose(ShapeDev sh, long long items)
 // of a tile pair, are flushed once per pair; otherwise they are int64.
 // ---------------------------------------------------------------------------
 constexpr int kGramWaves = 4;
+// The overlap kernel squares kSqBias + Q^2 instead of Q^2 (below), which adds
+// kSqBias^2 and 2 kSqBias Q^2 per element, in 64-bit integers modulo 2^64; it
+// takes the first off itself, the second is taken off here, where sum Q^2 is
+// formed: the record's sum Q^4 starts from -2 kSqBias sum Q^2.
+constexpr unsigned long long kSqBias = 0x4B000000ull;  // the bits of 2^23
 constexpr int kNarrowLt = 8192;  // the int32 epilogue: |G| <= 2^13
 // waves per SIMD: two where a wave's accumulators (RR x 2 x NV blocks of
 // 16 per lane) fit in half the register file, with the int32 epilogue
@@ -488,7 +492,9 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
         if (tid < PP) {
             unsigned long long q2 = 0;
             for (int d = 0; d < L; ++d) q2 += Fb[(tid * 2 + 0) * L + d];
-            sh.rec[((size_t)cfg * PP + tid) * rl + 2 * L + 1] = (int64_t)q2;
+            int64_t* const rp = sh.rec + ((size_t)cfg * PP + tid) * rl + 2 * L;
+            rp[1] = (int64_t)q2;
+            rp[2] = (int64_t)(0ull - 2 * kSqBias * q2);  // what the overlap kernel's squares add too much
         }
         for (int e = tid; e < PP * 2 * L; e += 64 * kGramWaves) {
             const int p = e / (2 * L), d = e % (2 * L);
@@ -500,277 +506,167 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
 }
 
 // ---------------------------------------------------------------------------
-// Q tiles: trQ and sum Q^4 for the NP pairs of launch group GI (records of
-// pairs a < b in lexicographic order; sum Q^2 comes from the Gram buckets).
+// Q tiles: trQ and sum Q^4 of every replica pair a < b (sum Q^2 comes from
+// the Gram buckets).
 //
-// Every wave works alone, with no LDS and no barrier: a 64 x 64 tile
-// (tau in 64T + [0, 64), tau' in 64T2 + [0, 64)) of each of its pairs as
-// 2 x 2 blocks of 32 x 32, the accumulators 64 registers per pair, two pairs
-// per launch, two waves per SIMD (one wave's MFMAs run while the other
-// builds its operands).  The operands come straight from each lane's
-// packed row words: in K step ks of chunk g, lane (i, h) of a block feeds
-// row i with bits 8j + 4h + m (j, m < 4) of the 32-bit half ks of its word,
-// one byte each, in the same order on both sides.  Row-side bytes are 4 B
-// (0 or 4), column-side bytes B, so the K steps sum 4 B^aT B^b; one more K
-// step adds X_tau + Y_tau' with X = h2 - 2 m^a_tau and
-// Y = (L^2 - h2) - 2 m^b_tau' (h2 = floor(L^2 / 2)), held as sixteen int8
-// pieces on one side against ones on the other.  The accumulator is then
-// Q itself: the epilogue squares it twice and adds.
+// A work item is a panel of 32 NU rows tau of one configuration, for every
+// pair (a, b) in turn.  For each a the workgroup expands the panel's rows of
+// replica a once into LDS, as fp4 operands of +-1 (16 bytes per lane, block
+// and chunk: the order in which the lanes read them back, without bank
+// conflicts); then each wave takes 64-column tiles tau' of each b > a alone,
+// with no barrier: NU x 2 blocks of 32 x 32, the column operands built in
+// registers from the bit rows (7 VALU per operand).  In chunk g lane (i, h)
+// of a block feeds row i with the 32 bits of half h of its word, in the same
+// order on both sides.  The fp32 accumulator is Q itself (|Q| <= L^2 <= 2^10,
+// exact): spins past L^2 and rows past Ltau are 0 on the row side, columns
+// past Ltau are +-0, so every element may enter the sum and no tile needs a
+// form of its own.  trQ = sum_tau (L^2 - 2 popcount(a ^ b)) needs no product.
 //
-// Waves form teams of wc.  Team t takes configurations t, t + nteams, ...;
-// its member j the tiles j, j + wc, ... of each, and it flushes its sums
-// once per configuration.  Workgroup b runs on XCD b mod nxcd, so a team
-// no larger than an XCD's share of waves reads its rows from one L2.
+// Two workgroups per CU, two waves per SIMD: one wave's MFMAs run while the
+// other forms Q^4, two instructions per element: 2^23 + Q^2 in fp32 (exact),
+// whose bits are kSqBias + Q^2, and a 32 x 32 + 64 bit multiply-add.
+//
+// At L = 24, Ltau = 2048, 4 replicas and 1024 configurations: 5.6 ms (3.7 of
+// them at the rate of the fp4 MFMAs at the 1.9 GHz that the power limit
+// leaves), against 12.8 ms with int8 MFMAs, every wave building both sides'
+// operands for two pairs, rank-one corrections in a K step of their own and
+// three instructions per Q^4.  One workgroup per item instead of a
+// persistent grid: 6.4 -> 6.0 ms (the dispatcher evens out the XCDs).
 // ---------------------------------------------------------------------------
-// The launch groups of the replica pairs (pair p = (a, b), a < b, in
-// lexicographic order): two pairs (a, b), (a, c) with the same row-side
-// replica per group, the pairs left over two at a time, the last alone.  A
-// group then builds 3 operand sets for its 4 MFMA blocks per K step.
-template <int RR>
-struct PairGroups {
-    static constexpr int PP = RR * (RR - 1) / 2;
-    int pair[PP] = {};   // pair indices in launch order
-    int first[PP] = {};  // first position of group k in pair[]
-    int size[PP] = {};   // pairs of group k (1 or 2)
-    int n = 0;           // groups
-    constexpr PairGroups() {
-        int left[PP] = {}, nl = 0, at = 0, p = 0;
-        for (int a = 0; a < RR; ++a) {
-            const int p0 = p, cnt = RR - 1 - a;
-            p += cnt;
-            int k = 0;
-            for (; k + 1 < cnt; k += 2) {
-                first[n] = at; size[n++] = 2;
-                pair[at++] = p0 + k;
-                pair[at++] = p0 + k + 1;
-            }
-            if (k < cnt) left[nl++] = p0 + k;
-        }
-        for (int k = 0; k < nl; k += 2) {
-            first[n] = at; size[n++] = k + 1 < nl ? 2 : 1;
-            pair[at++] = left[k];
-            if (k + 1 < nl) pair[at++] = left[k + 1];
-        }
-    }
-};
-constexpr int pair_row(int R, int p) {
-    int a = 0;
-    while (p >= R - 1 - a) { p -= R - 1 - a; ++a; }
-    return a;
-}
-constexpr int pair_col(int R, int p) {
-    int a = 0;
-    while (p >= R - 1 - a) { p -= R - 1 - a; ++a; }
-    return a + 1 + p;
-}
+constexpr int kOverlapWaves = 4;
 
-// Row-side and column-side replica slots of launch group GI (NP pairs).
-template <int RR, int GI, int NP>
-struct PairSides {
-    int na = 0, nb = 0;
-    int ra[RR] = {}, rb[RR] = {};  // replica of each row-side / column-side slot
-    int pa[NP] = {}, pb[NP] = {};  // slots of the group's pair p
-    int pi[NP] = {};               // record index of the group's pair p
-    constexpr PairSides() {
-        constexpr PairGroups<RR> grp{};
-        int sa[RR] = {}, sb[RR] = {};
-        for (int r = 0; r < RR; ++r) sa[r] = sb[r] = -1;
-        for (int k = 0; k < NP; ++k) {
-            const int p = grp.pair[grp.first[GI] + k];
-            const int a = pair_row(RR, p), b = pair_col(RR, p);
-            if (sa[a] < 0) { sa[a] = na; ra[na++] = a; }
-            if (sb[b] < 0) { sb[b] = nb; rb[nb++] = b; }
-            pa[k] = sa[a];
-            pb[k] = sb[b];
-            pi[k] = p;
-        }
-    }
-};
-
-constexpr int kTeamWaves = 4;  // waves per workgroup of the overlap kernel
-
-template <int RR, int GI, int NP>
-__global__ void __launch_bounds__(64 * kTeamWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_overlap_mfma(ShapeDev sh, int cfg0, int ncfg, int wc, int nxcd) {
-    constexpr PairSides<RR, GI, NP> ps{};
-    constexpr int NA = ps.na, NB = ps.nb;
-    constexpr int PP = RR * (RR - 1) / 2;
-    const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5, sh4 = 4 * h;
-    const int G = gridDim.x * kTeamWaves, gx = G / nxcd;
-    const int xcd = blockIdx.x % nxcd;
-    const int s = (blockIdx.x / nxcd) * kTeamWaves + (threadIdx.x >> 6);
-    int team, member;
-    if (wc <= gx) {
-        team = xcd * (gx / wc) + s / wc;
-        member = s % wc;
-    } else {
-        const int k = wc / gx;
-        team = xcd / k;
-        member = (xcd % k) * gx + s;
-    }
-    const int nteams = G / wc;
-    const int L2 = sh.L2, Lt = sh.Lt, nx = sh.nx, ntt = (Lt + 63) / 64, ntiles = ntt * ntt;
-    const int h2 = L2 >> 1;
+// NX: 0 for one chunk (L <= 8), 1 for an even number of them, 2 for an odd one.
+template <int NU, int NX>
+__global__ void __launch_bounds__(64 * kOverlapWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_overlap_mfma(ShapeDev sh, int cfg0, int ncfg, int npanel, int nsplit, int grouped) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    i32x4* const Aop = (i32x4*)smem;  // [nx][NU][64]
+    const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int L2 = sh.L2, Lt = sh.Lt, nx = sh.nx, R = sh.R, P = sh.P;
+    const int ntt = (Lt + 63) / 64;
     const int rl = 2 * sh.L + 3;
-    if (member >= ntiles) return;
-    for (int cfg = cfg0 + team; cfg < cfg0 + ncfg; cfg += nteams) {
-        unsigned long long s4[NP];
-        int tr[NP];
+    const int ipc = npanel * nsplit;
+    // grouped: workgroup b (on XCD b mod 8) takes the items of the
+    // configurations b mod 8, b mod 8 + 8, ..., so that a configuration's
+    // rows are read through one L2; otherwise the items in plain order
+    const int ng = grouped ? 8 : 1, grp = grouped ? (int)blockIdx.x & 7 : 0;
+    const int k = (int)blockIdx.x / ng;
+    {
+        if (grp + ng * (k / ipc) >= ncfg) return;
+        const int cfg = cfg0 + grp + ng * (k / ipc);
+        const int part = k % ipc / npanel, row0 = 32 * NU * (k % ipc % npanel);
+        const uint64_t* const px = sh.Px + (size_t)cfg * R * nx * Lt;
+        // uniform descriptor (readfirstlane is a signed int: cast before widening)
+        const uint32_t base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)px);
+        const uint32_t base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)px >> 32));
+        const __amdgpu_buffer_rsrc_t words = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(((uint64_t)base_hi << 32) | base_lo), (short)0, R * nx * Lt * 8, 0x00020000);
+        const int voff = 8 * i + 4 * h;
+        int p = 0;
+        for (int a = 0; a + 1 < R; ++a) {
+            __syncthreads();  // the waves have read the previous panel
+            for (int e = tid; e < nx * NU * 64; e += 64 * kOverlapWaves) {
+                const int g = e / (NU * 64), row = row0 + 32 * ((e >> 6) % NU) + (e & 31), hh = (e >> 5) & 1;
+                const bool ok = row < Lt;
+                const uint32_t x = ok ? ((const uint32_t*)px)[2 * (((size_t)a * nx + g) * Lt + row) + hh] : 0u;
+                const int nv = ok ? L2 - 64 * g - 32 * hh : 0;  // spins of this half
+                const uint32_t vm = nv >= 32 ? ~0u : (nv > 0 ? (1u << nv) - 1u : 0u);
+                i32x4 o;
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            s4[p] = 0;
-            tr[p] = 0;
-        }
-        const uint64_t* const px = sh.Px + (size_t)cfg * RR * nx * Lt;
-        for (int t = member; t < ntiles; t += wc) {
-            const int T = t / ntt, T2 = t - T * ntt;
-            // this lane's rows: tau = 64T + 32u + i (row side), 64T2 + 32v + i
-            // (column side), clamped into [0, Lt): a row past Lt only feeds
-            // elements of its own row or column, which the epilogue skips, and
-            // loads without a branch let the wait counts stay exact
-            const int ta0 = 64 * T + i, tb0 = 64 * T2 + i;
-            const int rowa[2] = {min(ta0, Lt - 1), min(ta0 + 32, Lt - 1)};
-            const int rowb[2] = {min(tb0, Lt - 1), min(tb0 + 32, Lt - 1)};
-            auto fetch = [&](int g, uint64_t (&wa)[2][NA], uint64_t (&wb)[2][NB]) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-#pragma unroll
-                    for (int a = 0; a < NA; ++a) wa[u][a] = px[((size_t)ps.ra[a] * nx + g) * Lt + rowa[u]];
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) wb[u][b] = px[((size_t)ps.rb[b] * nx + g) * Lt + rowb[u]];
+                for (int m = 0; m < 4; ++m)
+                    o[m] = (int)(((x << (3 - m)) & 0x88888888u) | (((vm >> m) & 0x11111111u) << 1));
+                Aop[e] = o;
+            }
+            __syncthreads();
+            for (int b = a + 1; b < R; ++b, ++p) {
+                unsigned long long s4 = 0;
+                int tr = 0;
+                if (part == 0) {
+                    for (int e = tid; e < nx * NU * 32; e += 64 * kOverlapWaves) {
+                        const int g = e / (NU * 32), row = row0 + e % (NU * 32);
+                        if (row < Lt)
+                            tr += (g == 0 ? L2 : 0) - 2 * (int)__popcll(px[((size_t)a * nx + g) * Lt + row] ^
+                                                                         px[((size_t)b * nx + g) * Lt + row]);
+                    }
                 }
-            };
-            v16i acc[NP][2][2];
+                const int step = kOverlapWaves * nsplit;
+                // the words of chunk g of tile t (kept below the last tile, so
+                // that the scalar offset stays inside the descriptor and rows
+                // past its end read 0)
+                auto fetch = [&](int t, int g, uint32_t (&w)[2]) {
+                    const int so = ((b * nx + g) * Lt + 64 * min(t, ntt - 1)) * 8;
+                    w[0] = __builtin_amdgcn_raw_buffer_load_b32(words, voff, so, 0);
+                    w[1] = __builtin_amdgcn_raw_buffer_load_b32(words, voff + 256, so, 0);
+                };
+                // Two operand sets and two word sets in turn, by the parity of
+                // the chunk: while a chunk's MFMAs run, the next one's row
+                // operands come from LDS, its column operands are built, and
+                // the words of the chunk after the next but one are loaded
+                // (those of the next tile's chunks 0 and 1 at the end).
+                f32x16 acc[NU][2];
+                i32x4 A0[NU], A1[NU], B0[2], B1[2];
+                uint32_t w0[2], w1[2];
+                int T = part * kOverlapWaves + wv;
+                auto load = [&](int t, int g, uint32_t (&w)[2], int slot, i32x4 (&A)[NU], i32x4 (&B)[2]) {
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
+                    for (int u = 0; u < NU; ++u) A[u] = Aop[(g * NU + u) * 64 + lane];
 #pragma unroll
                     for (int v = 0; v < 2; ++v)
+                        B[v] = fp4_signs_operand(w[v], 64 * t + 32 * v + i < Lt ? 0x22222222u : 0u);
+                    const bool here = g + 2 < nx;
+                    fetch(here ? t : t + step, here ? g + 2 : min(slot, nx - 1), w);
+                };
+                auto mul = [&](const i32x4 (&A)[NU], const i32x4 (&B)[2], auto firstC) {
+                    constexpr bool kFirst = decltype(firstC)::value;
 #pragma unroll
-                        for (int q = 0; q < 16; ++q) acc[p][u][v][q] = 0;
-            int ma[2][NA], mb[2][NB];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-#pragma unroll
-                for (int a = 0; a < NA; ++a) ma[u][a] = 0;
-#pragma unroll
-                for (int b = 0; b < NB; ++b) mb[u][b] = 0;
-            }
-            auto chunk = [&](const uint64_t (&wa)[2][NA], const uint64_t (&wb)[2][NB]) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-#pragma unroll
-                    for (int a = 0; a < NA; ++a) ma[u][a] += __popcll(wa[u][a]);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) mb[u][b] += __popcll(wb[u][b]);
-                }
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    v4i A[2][NA], B[2][NB];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-                        for (int a = 0; a < NA; ++a)
-                            A[u][a] = mfma_bits_operand<true>((uint32_t)(wa[u][a] >> (32 * ks)) >> sh4);
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-                            B[u][b] = mfma_bits_operand<false>((uint32_t)(wb[u][b] >> (32 * ks)) >> sh4);
-                    }
-#pragma unroll
-                    for (int p = 0; p < NP; ++p)
-#pragma unroll
-                        for (int u = 0; u < 2; ++u)
-#pragma unroll
-                            for (int v = 0; v < 2; ++v)
-                                acc[p][u][v] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                                    A[u][ps.pa[p]], B[v][ps.pb[p]], acc[p][u][v], 0, 0, 0);
-                }
-            };
-            // two word sets in turn, the next chunk's loads in flight during
-            // this chunk's MFMAs; the loop body is one straight block (past
-            // the last chunk a fetch reloads it) so that the loads stay ahead
-            // of their uses and the wait counts are fixed
-            uint64_t w0a[2][NA], w0b[2][NB], w1a[2][NA], w1b[2][NB];
-            fetch(0, w0a, w0b);
-            for (int g = 0; g + 1 < nx; g += 2) {
-                fetch(g + 1, w1a, w1b);
-                chunk(w0a, w0b);
-                fetch(min(g + 2, nx - 1), w0a, w0b);
-                chunk(w1a, w1b);
-            }
-            if (nx & 1) chunk(w0a, w0b);
-            // the correction step: X on the row side's first half-wave, Y on
-            // the column side's second, ones against them
-            {
-                const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
-                v4i A[2][NA], B[2][NB];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-#pragma unroll
-                    for (int a = 0; a < NA; ++a) A[u][a] = h ? ones : mfma_pieces16(h2 - 2 * ma[u][a]);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) B[u][b] = h ? mfma_pieces16(L2 - h2 - 2 * mb[u][b]) : ones;
-                }
-#pragma unroll
-                for (int p = 0; p < NP; ++p)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
+                    for (int u = 0; u < NU; ++u)
 #pragma unroll
                         for (int v = 0; v < 2; ++v)
-                            acc[p][u][v] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                                A[u][ps.pa[p]], B[v][ps.pb[p]], acc[p][u][v], 0, 0, 0);
-            }
-            // epilogue: |Q| <= L^2, Q^2 < 2^20, Q^4 < 2^40
-            if (64 * (T + 1) <= Lt && 64 * (T2 + 1) <= Lt && T != T2) {
+                            acc[u][v] = mfma_fp4(fp4_wide(A[u]), fp4_wide(B[v]), kFirst ? f32x16{} : acc[u][v]);
+                };
+                fetch(T, 0, w0);
+                fetch(T, min(1, nx - 1), w1);
+                load(T, 0, w0, 0, A0, B0);
+                for (; T < ntt; T += step) {
+                    if constexpr (NX > 0) load(T, 1, w1, 1, A1, B1);
+                    mul(A0, B0, std::true_type{});
+                    if constexpr (NX > 0) {
+                        int g = 1;
+                        for (; g + 2 < nx; g += 2) {
+                            load(T, g + 1, w0, 0, A0, B0);
+                            mul(A1, B1, std::false_type{});
+                            load(T, g + 2, w1, 1, A1, B1);
+                            mul(A0, B0, std::false_type{});
+                        }
+                        if constexpr (NX == 2) load(T, g + 1, w0, 0, A0, B0);
+                        mul(A1, B1, std::false_type{});
+                        if constexpr (NX == 2) mul(A0, B0, std::false_type{});
+                    }
+                    load(T + step, 0, w0, 0, A0, B0);
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
+                    for (int u = 0; u < NU; ++u)
 #pragma unroll
                         for (int v = 0; v < 2; ++v)
 #pragma unroll
                             for (int q = 0; q < 16; ++q) {
-                                const int qv = acc[p][u][v][q];
-                                const uint32_t q2 = (uint32_t)__mul24(qv, qv);
-                                s4[p] += (unsigned long long)q2 * q2;
+                                // 2^23 + Q^2 is exact; its bits are kSqBias + Q^2
+                                const uint32_t q2 =
+                                    __float_as_uint(__builtin_fmaf(acc[u][v][q], acc[u][v][q], 8388608.0f));
+                                s4 += (unsigned long long)q2 * q2;
                             }
-            } else {
+                    s4 -= (unsigned long long)(NU * 32) * kSqBias * kSqBias;
+                }
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) {
-                        const int col = 64 * T2 + 32 * v + i;
-#pragma unroll
-                        for (int q = 0; q < 16; ++q) {
-                            const int row = 64 * T + 32 * u + 8 * (q >> 2) + 4 * h + (q & 3);
-                            if (row >= Lt || col >= Lt) continue;
-#pragma unroll
-                            for (int p = 0; p < NP; ++p) {
-                                const int qv = acc[p][u][v][q];
-                                const uint32_t q2 = (uint32_t)__mul24(qv, qv);
-                                s4[p] += (unsigned long long)q2 * q2;
-                                if (row == col) tr[p] += qv;
-                            }
-                        }
-                    }
-            }
-        }
-        // per-configuration flush: wave reduction, one atomic per value
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                s4[p] += (unsigned long long)__shfl_xor((long long)s4[p], off, 64);
-                tr[p] += __shfl_xor(tr[p], off, 64);
-            }
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                unsigned long long* rp = (unsigned long long*)(sh.rec + ((size_t)cfg * PP + ps.pi[p]) * rl);
-                atomicAdd(rp + 2 * sh.L, (unsigned long long)(long long)tr[p]);
-                atomicAdd(rp + 2 * sh.L + 2, s4[p]);
+                for (int off = 32; off > 0; off >>= 1) {
+                    s4 += (unsigned long long)__shfl_xor((long long)s4, off, 64);
+                    tr += __shfl_xor(tr, off, 64);
+                }
+                if (lane == 0) {
+                    unsigned long long* rp = (unsigned long long*)(sh.rec + ((size_t)cfg * P + p) * rl);
+                    if (part == 0) atomicAdd(rp + 2 * sh.L, (unsigned long long)(long long)tr);
+                    atomicAdd(rp + 2 * sh.L + 2, s4);
+                }
             }
         }
     }
@@ -893,17 +789,39 @@ size_t gram_lds(int RR, int L) {
     const int nxp = 64 * ((L * L + 63) / 64);
     return (size_t)2 * PP * 2 * L * 8 + (size_t)RR * nxp * 4;
 }
-// Launch groups GI .. of RR replicas, one launch each.
-template <int RR, int GI>
-hipError_t launch_overlap(const ShapeDev& sh, int cfg0, int ncfg, int grid, int wc, int nxcd, hipStream_t st) {
-    constexpr PairGroups<RR> grp{};
-    constexpr int n = grp.size[GI];
-    hipLaunchKernelGGL((k_overlap_mfma<RR, GI, n>), dim3(grid), dim3(64 * kTeamWaves), 0, st, sh, cfg0, ncfg,
-                       wc, nxcd);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if constexpr (GI + 1 < grp.n) return launch_overlap<RR, GI + 1>(sh, cfg0, ncfg, grid, wc, nxcd, st);
-    return hipSuccess;
+// Panels of 128 rows where Ltau fills them, else of 64.  The items of a short
+// range are split along the columns until they fill two workgroups per CU.
+template <int NU, int NX>
+hipError_t launch_overlap_nx(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStream_t st) {
+    static bool lds_set = false;
+    if (!lds_set) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_overlap_mfma<NU, NX>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 16 * NU * 64 * 16);
+        if (e != hipSuccess) return e;
+        lds_set = true;
+    }
+    const int npanel = (sh.Lt + 32 * NU - 1) / (32 * NU), ntt = (sh.Lt + 63) / 64;
+    int nsplit = 1;
+    while ((long long)ncfg * npanel * nsplit < 2 * ncu && kOverlapWaves * nsplit < ntt) nsplit *= 2;
+    const bool grouped = ncu % 8 == 0 && ncfg >= 128;
+    const long long items = (long long)ncfg * npanel * nsplit;
+    const long long grid = grouped ? (long long)((ncfg + 7) / 8) * 8 * npanel * nsplit : items;
+    hipLaunchKernelGGL((k_overlap_mfma<NU, NX>), dim3((unsigned)grid), dim3(64 * kOverlapWaves), (size_t)sh.nx * NU * 64 * 16, st, sh,
+                       cfg0, ncfg, npanel, nsplit, (int)grouped);
+    return hipGetLastError();
+}
+
+template <int NU>
+hipError_t launch_overlap_nu(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStream_t st) {
+    if (sh.nx == 1) return launch_overlap_nx<NU, 0>(sh, cfg0, ncfg, ncu, st);
+    return sh.nx % 2 == 0 ? launch_overlap_nx<NU, 1>(sh, cfg0, ncfg, ncu, st)
+                          : launch_overlap_nx<NU, 2>(sh, cfg0, ncfg, ncu, st);
+}
+
+hipError_t launch_overlap(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStream_t st) {
+    const int n64 = (sh.Lt + 63) / 64;
+    return n64 == 1 || n64 == 3 ? launch_overlap_nu<2>(sh, cfg0, ncfg, ncu, st)
+                                : launch_overlap_nu<4>(sh, cfg0, ncfg, ncu, st);
 }
 
 template <int RR>
@@ -945,18 +863,7 @@ hipError_t launch_mfma(const ShapeDev& sh, int cfg0, int ncfg, hipStream_t st) {
                            gram_lds(RR, sh.L), st, sh, cfg0, ncfg);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // overlap: two workgroups of kTeamWaves waves per CU; teams of wc waves,
-    // an XCD's share (a power-of-two fraction of it while a configuration
-    // has fewer tiles, a multiple while there are fewer configurations than
-    // teams)
-    const int nxcd = ncu % 8 == 0 ? 8 : 1;
-    const int G = kTeamWaves * 2 * ncu, gx = G / nxcd;
-    const int ntt = (sh.Lt + 63) / 64, ntiles = ntt * ntt;
-    int wc = gx;
-    while (wc % 2 == 0 && wc / 2 >= ntiles) wc /= 2;
-    auto fits = [&](int w) { return w <= gx ? gx % w == 0 : (w % gx == 0 && nxcd % (w / gx) == 0); };
-    while (wc < G && G / wc > ncfg && fits(2 * wc)) wc *= 2;
-    return launch_overlap<RR, 0>(sh, cfg0, ncfg, 2 * ncu, wc, nxcd, st);
+    return launch_overlap(sh, cfg0, ncfg, ncu, st);
 }
 
 }  // namespace

@@ -169,6 +169,26 @@ __device__ __forceinline__ i32x8 fp4_bits_operand(uint32_t x) {
     return __builtin_shufflevector(o, o, 0, 1, 2, 3, -1, -1, -1, -1);
 }
 
+// Bit 4j + m of x (m < 4, j < 8) as the fp4 nibble j of register m: -1 where
+// the bit is set, else +1 (mag = 0x22222222: e2m1 1.0 is 0010, the bit goes to
+// the sign), or +-0 (mag = 0).  mag sits in a vector register, so that each
+// register takes one shift and one v_bitop3 ((x & signs) | mag), 7 in all.
+__device__ __forceinline__ i32x4 fp4_signs_operand(uint32_t x, uint32_t mag) {
+    i32x4 o;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) o[m] = (int)__builtin_amdgcn_bitop3_b32(x << (3 - m), 0x88888888u, mag, 0xEA);
+    return o;
+}
+// The fp4 form reads only the lower four registers of an operand.
+__device__ __forceinline__ i32x8 fp4_wide(i32x4 o) {
+    return __builtin_shufflevector(o, o, 0, 1, 2, 3, -1, -1, -1, -1);
+}
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+// One unscaled v_mfma_f32_32x32x64_f8f6f4 on fp4 operands: 64 values of K.
+__device__ __forceinline__ f32x16 mfma_fp4(i32x8 a, i32x8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, kFp4, kFp4, 0, 0, 0, 0);
+}
+
 // Sixteen int8 bytes summing to v, |v| <= 1792: fifteen of floor(v / 16) and
 // one of floor(v / 16) + (v mod 16).  Against sixteen ones on the other side
 // of one K step it adds v to every element of a row (or column).

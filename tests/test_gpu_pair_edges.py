@@ -1,0 +1,74 @@
+"""Pair records at the edges of the measurement kernels' tiles, exactly
+against the oracle's integer reductions: one, an even and an odd number of
+64-bit chunks along L^2; Ltau around the 64- and 128-row panels; ranges that
+start and end inside a panel of configurations, below and above 128
+configurations; and configurations at the extremes (all spins equal, |Q| =
+L^2 and |G| = Ltau everywhere)."""
+import numpy as np
+import pytest
+
+from paper_2310_07486_amd import tfim
+from paper_2310_07486_amd.workloads import Shape, ladder
+
+pytestmark = pytest.mark.gpu
+
+
+def _spins(plan, sh, cfg):
+    """S[r] = +-1 matrix [L^2][Ltau] of configuration cfg = i * samples + s."""
+    words = plan.export_spins(0)  # [r][w][j][tau][xy]
+    kidx, _ = plan.get_state(0)  # [r][s][w]
+    i, s = divmod(cfg, sh.n_samples)
+    out = []
+    for r in range(sh.n_replicas):
+        w = int(np.nonzero(kidx[r, s] == i)[0][0])
+        out.append(tfim.unpack_lane(words[r, w, s // 64], s % 64).T.astype(np.int64))
+    return out
+
+
+def _records(S, L):
+    """[pair][2L+3] of the +-1 matrices S of every replica, plain int64 numpy."""
+    G = [s @ s.T for s in S]
+    xy = np.arange(L * L)
+    dx = (xy[:, None] % L - xy[None, :] % L) % L
+    dy = (xy[:, None] // L - xy[None, :] // L) % L
+    rows = []
+    for a in range(len(S)):
+        for b in range(a + 1, len(S)):
+            H = G[a] * G[b]
+            Q = S[a].T @ S[b]
+            rows.append([int(H[dx == d].sum()) for d in range(L)] + [int(H[dy == d].sum()) for d in range(L)] +
+                        [int(np.trace(Q)), int((Q ** 2).sum()), int((Q ** 4).sum())])
+    return np.array(rows, dtype=np.int64)
+
+
+@pytest.mark.parametrize("L,Lt,R,cfg0,ncfg", [
+    (2, 16, 2, 5, 1), (4, 64, 6, 0, 3), (6, 72, 3, 60, 9), (8, 128, 2, 0, 1), (8, 136, 5, 17, 2),
+    (10, 192, 2, 3, 2), (12, 200, 6, 100, 2), (14, 256, 3, 126, 2), (16, 264, 4, 1, 130), (18, 320, 2, 0, 128),
+    (20, 104, 6, 63, 2), (22, 56, 3, 8, 1), (24, 448, 4, 90, 2), (24, 520, 2, 127, 1)])
+def test_pair_records_at_tile_edges(L, Lt, R, cfg0, ncfg):
+    print(f"pair edges L={L} Ltau={Lt} R={R} cfg0={cfg0} ncfg={ncfg}", flush=True)
+    sh = Shape(L, Lt, 1, R, ladder(0.25, 0.4, 3))
+    plan = tfim.Plan([sh], 31 * L + Lt)
+    plan.init()
+    plan.sweep(5)
+    got = plan.measure_range(0, 0, cfg0, ncfg)
+    for c in sorted({0, ncfg // 2, ncfg - 1}):
+        assert np.array_equal(got[c], _records(_spins(plan, sh, cfg0 + c), L)), c
+    plan.close()
+
+
+@pytest.mark.parametrize("L,Lt", [(8, 64), (12, 136), (20, 192), (24, 2048)])
+def test_pair_records_of_equal_spins(L, Lt):
+    """Every Q = +-L^2 and every G = Ltau: closed form."""
+    print(f"pair extremes L={L} Ltau={Lt}", flush=True)
+    sh = Shape(L, Lt, 1, 3, [0.3])
+    plan = tfim.Plan([sh], 9)
+    plan.init_couplings(0)
+    S = np.zeros((3, 1, 1, Lt, L * L), dtype=np.uint64)
+    S[2] = ~np.uint64(0)  # replica 2 flipped against the others
+    plan.init_spins(0, S)
+    got = plan.measure_range(0, 0, 0, 64)
+    for p, sign in ((0, 1), (1, -1), (2, -1)):
+        want = [Lt * Lt * L ** 3] * (2 * L) + [sign * L * L * Lt, Lt * Lt * L ** 4, Lt * Lt * L ** 8]
+        assert np.array_equal(got[:, p], np.tile(np.array(want, dtype=np.int64), (64, 1)))
+    plan.close()
