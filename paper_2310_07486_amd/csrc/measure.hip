@@ -20,12 +20,11 @@
 //
 // 1. k_transpose turns the multispin words (64 samples per word) into one
 //    bit row per sample, in two layouts: bits along tau (Pt, the K axis of G)
-//    and bits along xy (Px, the K axis of Q), by 64x64 bit transposes across
+//    and bits along the sites (Px, the K axis of Q), by 64x64 bit transposes across
 //    a wavefront (six xor-shuffle butterfly stages).
-// 2. k_gram_mfma: one workgroup per configuration at a time, 64x64 tiles of
-//    G (upper triangle of tile pairs), all replicas at once, bucket sums in
-//    LDS, flushed once per configuration; for Ltau <= 8192 on fp4 MFMAs
-//    (v_mfma_scale_f32_32x32x64_f8f6f4: {0, 0.5} operands, exact in fp32).
+// 2. k_gram_mfma: 64x64 tiles of G (upper triangle of tile pairs), the
+//    replicas one after the other on fp4 MFMAs and kept as int16, bucket sums
+//    in LDS; k_gram_wide (int8 MFMAs, int64 products) for Ltau > 8192.
 // 3. k_overlap_mfma: panels of rows tau of one configuration, every pair in
 //    turn, on fp4 MFMAs with +-1 operands (Q itself in the accumulators), the
 //    row operands expanded once per panel into LDS, the column operands built
@@ -43,7 +42,6 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 
 
 constexpr int kMaxR = 6;       // replicas handled by the MFMA kernels
@@ -59,9 +57,14 @@ __global__ void __launch_bounds__(256) k_transpose(ShapeDev sh, long long items)
     const int L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, W = sh.W, R = sh.R;
     const int S = 64 * W;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    for (long long item = blockIdx.x; item < items; item += gridDim.x) {
-        const int g = (int)(item % sh.nx);
-        const long long rest = item / sh.nx;
+    // Workgroup b runs on XCD b mod 8: an XCD takes all nx tiles of one
+    // (configuration, chunk) in turn, since they share cache lines of S (a
+    // tile reads 32-byte pieces of every tau plane).
+    const int xcd = blockIdx.x & 7;
+    for (long long n = blockIdx.x >> 3;; n += gridDim.x >> 3) {
+        const int g = (int)(n % sh.nx);
+        const long long rest = n / sh.nx * 8 + xcd;
+        if (rest * sh.nx >= items) break;
         const int c = (int)(rest % sh.nc);
         const int cfg = (int)(rest / sh.nc);  // (r*nk + w)*W + j
         const int j = cfg % W, rw = cfg / W, w = rw % nk, r = rw / nk;
@@ -74,11 +77,14 @@ __global__ void __launch_bounds__(256) k_transpose(ShapeDev sh, long long items)
         // the 64 x 64 words of the tile: all 16 loads of a thread in flight
         // at once (the loops are unrolled so that they can be)
         uint64_t v[16];
+        int x1, x2;
+        slot_site(sh.L, 64 * g + lane, x1, x2);
+        const bool site_ok = 64 * g + lane < L2;
+        const uint64_t* const col = sh.S + (size_t)cfg * Lt * L2 + (site_ok ? x1 + sh.L * x2 : 0);
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            const int e = tid + 256 * k;
-            const int t = e >> 6, u = e & 63, tau = 64 * c + t, xy = 64 * g + u;
-            v[k] = (tau < Lt && xy < L2) ? sh.S[((size_t)cfg * Lt + tau) * L2 + xy] : 0ull;
+            const int tau = 64 * c + wv + 4 * k;
+            v[k] = (tau < Lt && site_ok) ? col[(size_t)tau * L2] : 0ull;
         }
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
@@ -125,39 +131,48 @@ __global__ void __launch_bounds__(256) k_transpose(ShapeDev sh, long long items)
 }
 
 // ---------------------------------------------------------------------------
-// G tiles and the D buckets.
+// G tiles and the D buckets (Ltau <= 8192).
 //
-// One workgroup takes one configuration at a time.  It first counts the
-// down spins n^r_x of every site row (popcount along tau) into LDS; then its
-// four waves share the tile pairs (X, Y), X <= Y, of the upper triangle,
-// each wave alone (no barrier inside a configuration), one wave per SIMD:
-// the 2 x 2 blocks of 32 x 32 of every replica's G^r = S S^T, accumulators
-// in the AGPRs, K = tau in chunks of 64, the {0,1} operands built in
-// registers from each lane's bit row.  With the int32 epilogue (NARROW), up
-// to 4 replicas and more configurations than CUs, two workgroups share a
-// CU, two waves a SIMD (one's MFMAs run while the other builds operands),
-// each wave on half a tile pair (the 2 x 1 blocks of a column half) above 2
-// replicas.  The epilogue forms
-// G = Ltau - 2 (n_x + n_y) + 4 (B B^T)_xy and the products G^a G^b.
+// Sites stand in blocks of 32 rows: block (a, b) holds x1 = 4a .. 4a + 3 and
+// x2 = 8b .. 8b + 7 (row 4 (x2 - 8b) + x1 - 4a), so that the 16 elements q of
+// a lane in the 32 x 32 MFMA layout take four values of x1 - y1 (by q mod 4)
+// and four of x2 - y2 (by q div 4), for every even L.  Blocks are taken two
+// at a time: a tile is 2 x 2 blocks, tiles X <= Y of the upper triangle.
 //
-// An element (x, y) of an off-diagonal pair stands for (y, x) too, with the
-// displacements negated; its products go to U, those of the diagonal
-// blocks of diagonal pairs to F, and the flush folds D[d] = F[d] + U[d] +
-// U[-d mod L].  In a diagonal pair the block (rows 32.., columns 0..31) is
-// the mirror of (rows 0.., columns 32..): only the latter is computed, into
-// U.
+// Each wave works alone on one tile (no barrier inside it), the replicas in
+// turn: the K loop of one replica runs on 64 fp32 accumulators (fp4 operands
+// of +-1 built in registers from the bit rows along tau, 7 VALU per operand
+// and one operand per MFMA), and its G is kept as packed int16 in 32
+// registers, so that all replicas of the tile fit at two waves per SIMD.  The
+// accumulators start from 1.5 2^23: the low 16 bits of each are then G itself
+// (|G| <= Ltau <= 2^13, exact) and two of them pack in one instruction.
+// Rows and columns of sites past L are 0, the bits past Ltau of the last
+// chunk cancel (half of them turned over on the row side).
 //
-// BLK (L a multiple of 8): tile X holds the 8 x 8 block of sites
-// (bx, by) = (X mod L/8, X div L/8), row r the site (8bx + r mod 8,
-// 8by + r div 8).  The 16 elements of a lane then take 4 values of x1 - y1
-// (one per q mod 4) and 4 of x2 - y2 (one per q div 4), so each lane sums
-// them in registers and adds 8 bucket values per pair and block, not 32.
-// Otherwise tile X holds the sites 64X .. 64X + 63 and every element adds
-// its own two.
+// The epilogue forms, per block and replica pair, the sums of G^a G^b over
+// the elements of equal x1 - y1 (v_mad_i32_i16) and of equal x2 - y2
+// (v_dot2_i32_i16), in int32 (at most 4 products, < 2^28), and adds these 8
+// values to int64 buckets in LDS.  Each bucket has ncopy copies, so that the
+// lanes of a wave that share a bucket do not meet at one address; pair p is
+// the fastest index (an immediate offset).
 //
-// NARROW (BLK and Ltau <= 8192): the products and the lane sums are int32
-// (24-bit multiplies), and a lane's x1 - y1 sums, the same in every block
-// of a tile pair, are flushed once per pair; otherwise they are int64.
+// An element (x, y) of an off-diagonal block stands for (y, x) too, with the
+// displacements negated; its products go to U, those of the diagonal blocks
+// to F, and the flush folds D[d] = F[d] + U[d] + U[-d mod L].  In a diagonal
+// tile the block (1, 0) is the mirror of (0, 1) and is dropped.
+//
+// A workgroup takes ncw configurations at a time (as many as keep its four
+// waves busy) or every nsplit-th part of the tiles of one; records are added
+// to.
+//
+// Bound by the words' way from L2 (the loads wait 0.4 of the wave cycles; the
+// matrix cores are busy 0.4).  L = 24, Ltau = 2048, 4 replicas, 1024
+// configurations: 1.85 ms with every replica's accumulators at once (64 x 32
+// tiles, {0, 0.5} operands, a popcount pass) -> 1.70 as above on rows in
+// site order -> 1.19 with the blocks' rows consecutive -> 1.02 with loads
+// four chunks ahead -> 0.90 with whole words per lane.  L = 12, Ltau = 512,
+// 6 replicas, 1536 configurations, where every element went to its own LDS
+// bucket before: 1.13 ms -> 0.19.
 // ---------------------------------------------------------------------------
 constexpr int kGramWaves = 4;
 // The overlap kernel squares kSqBias + Q^2 instead of Q^2 (below), which adds
@@ -165,16 +180,223 @@ constexpr int kGramWaves = 4;
 // takes the first off itself, the second is taken off here, where sum Q^2 is
 // formed: the record's sum Q^4 starts from -2 kSqBias sum Q^2.
 constexpr unsigned long long kSqBias = 0x4B000000ull;  // the bits of 2^23
-constexpr int kNarrowLt = 8192;  // the int32 epilogue: |G| <= 2^13
-// waves per SIMD: two where a wave's accumulators (RR x 2 x NV blocks of
-// 16 per lane) fit in half the register file, with the int32 epilogue
-constexpr int gram_wpe(int RR, int NV, bool narrow) { return narrow && RR * NV <= 4 ? 2 : 1; }
+constexpr int kNarrowLt = 8192;  // |G| <= 2^13: int16 digits, int32 lane sums
+__host__ __device__ constexpr int gram_pitch(int P) { return P | 1; }  // pairs, padded to an odd count
 
-template <int RR, int NV, bool BLK, bool NARROW>
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int mad_lo16(int a, int b, int c) {
+    int d;
+    asm("v_mad_i32_i16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ int mad_hi16(int a, int b, int c) {
+    int d;
+    asm("v_mad_i32_i16 %0, %1, %2, %3 op_sel:[1,1,0,0]" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ int dot16(int a, int b, int c) {
+    return __builtin_amdgcn_sdot2(__builtin_bit_cast(i16x2, a), __builtin_bit_cast(i16x2, b), c, false);
+}
+
+template <int RR>
+__global__ void __launch_bounds__(64 * kGramWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_gram_mfma(ShapeDev sh, int cfg0, int ncfg, int ncw, int nsplit, int ncopy, int grouped) {
+    constexpr int PP = RR * (RR - 1) / 2, PT = gram_pitch(PP);
+    extern __shared__ __align__(16) uint8_t smem[];
+    unsigned long long* const Bk = (unsigned long long*)smem;  // [ncw][F, U][x, y][L][ncopy][PT]
+    const int L = sh.L, Lt = sh.Lt, nc = sh.nc, nxp = sh.nxp;
+    const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb8 = (L + 7) >> 3, nblk = ((L + 3) >> 2) * nb8;
+    const int ntile = (nblk + 1) >> 1, ntp = ntile * (ntile + 1) / 2;
+    // grouped: workgroup b runs on XCD b mod 8, which takes the configurations
+    // b mod 8, b mod 8 + 8, ... (times ncw), so that the nsplit workgroups of one
+    // read its rows through one L2
+    const int ng = grouped ? 8 : 1, item = (int)blockIdx.x / ng;
+    const int part = item % nsplit, c0 = (item / nsplit * ng + (grouped ? (int)blockIdx.x & 7 : 0)) * ncw;
+    if (c0 >= ncfg) return;
+    const int ncl = min(ncw, ncfg - c0);
+    const int half = 2 * L * ncopy * PT;  // words of F or of U of one configuration
+    for (int e = tid; e < ncl * 2 * half; e += 64 * kGramWaves) Bk[e] = 0;
+    __syncthreads();
+    // Lane (i, h) takes the whole word of chunk 2c + h, whose halves feed two
+    // MFMAs: one 8-byte load per row and 128 values of tau, 256 consecutive
+    // bytes per half-wave.  In the last pair: the last chunk's bits past Ltau
+    // (half of them turned over; their number is a multiple of 8), and with an
+    // odd number of chunks the half-wave h = 1 counts for nothing.
+    const int padn = (64 * nc - Lt) >> 1;
+    const uint64_t flip64 = padn && h == ((nc - 1) & 1) ? ~0ull << (64 - padn) : 0ull;
+    const uint32_t flip[2] = {(uint32_t)flip64, (uint32_t)(flip64 >> 32)};
+    const bool beyond = (nc & 1) && h == 1;
+    const uint32_t in_last = beyond ? 0u : ~0u;
+    const int back_last = beyond ? 8 * nxp : 0;  // such lanes read the last chunk instead
+    f32x16 start;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) start[q] = 12582912.0f;
+    for (int unit = part * kGramWaves + wv; unit < ncl * ntp; unit += kGramWaves * nsplit) {
+        const int cl = unit / ntp;
+        int X = 0, rem = unit - cl * ntp;
+        while (rem >= ntile - X) { rem -= ntile - X; ++X; }
+        const int Y = X + rem;
+        const uint64_t* const pt = sh.Pt + (size_t)(cfg0 + c0 + cl) * RR * nc * nxp;
+        const uint32_t base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)pt);
+        const uint32_t base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)pt >> 32));
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(((uint64_t)base_hi << 32) | base_lo), (short)0, RR * nc * nxp * 8, 0x00020000);
+        int voff[4];         // byte offset of this lane's row (chunk h of a pair) in the row blocks, then the columns
+        uint32_t mag[4];     // 0 on a padding site
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int blk = 2 * (k < 2 ? X : Y) + (k & 1);
+            const int x1 = 4 * (blk / nb8) + (i & 3), x2 = 8 * (blk % nb8) + (i >> 2);
+            const bool ok = blk < nblk && x1 < L && x2 < L;
+            voff[k] = 8 * ((ok ? site_slot(L, x1, x2) : 0) + h * nxp);
+            mag[k] = ok ? 0x22222222u : 0u;
+        }
+        int pk[RR][2][2][8];  // G of elements 2t, 2t + 1
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+            f32x16 acc[2][2];
+            auto fetch = [&](int c, u32x2 (&w)[4]) {
+                const int so = (r * nc + 2 * c) * nxp * 8;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) w[k] = __builtin_amdgcn_raw_buffer_load_b64(rows, voff[k], so, 0);
+            };
+            auto chunk = [&](const u32x2 (&w)[4], auto firstC) {
+                constexpr bool kFirst = decltype(firstC)::value;
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    i32x4 o[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        o[k] = fp4_signs_operand(kFirst && k < 2 ? w[k][ks] ^ flip[ks] : w[k][ks],
+                                                 kFirst && k < 2 ? mag[k] & in_last : mag[k]);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int v = 0; v < 2; ++v)
+                            acc[u][v] = mfma_fp4(fp4_wide(o[u]), fp4_wide(o[2 + v]),
+                                                 kFirst && ks == 0 ? start : acc[u][v]);
+                }
+            };
+            // the last pair of chunks first (it starts the accumulators), then
+            // pairs 0 .. n - 1, two word sets in turn, each loaded two pairs
+            // ahead (past the end: the last one again, not used)
+            const int n = (nc + 1) / 2 - 1;
+            u32x2 w0[4], w1[4];
+            {
+                const int so = (r * nc + 2 * n) * nxp * 8;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    w1[k] = __builtin_amdgcn_raw_buffer_load_b64(rows, voff[k] - back_last, so, 0);
+            }
+            fetch(0, w0);
+            chunk(w1, std::true_type{});
+            fetch(min(1, n), w1);
+            int c = 0;
+            for (; c + 1 < n; c += 2) {
+                chunk(w0, std::false_type{});
+                fetch(min(c + 2, n), w0);
+                chunk(w1, std::false_type{});
+                fetch(min(c + 3, n), w1);
+            }
+            if (c < n) chunk(w0, std::false_type{});
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v)
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        pk[r][u][v][t] = (int)__builtin_amdgcn_perm(__float_as_uint(acc[u][v][2 * t + 1]),
+                                                                    __float_as_uint(acc[u][v][2 * t]), 0x05040100u);
+                        asm volatile("" : "+v"(pk[r][u][v][t]));  // packed here, not where it is used
+                    }
+            __builtin_amdgcn_sched_barrier(0);  // the next replica's loads wait until the accumulators are free
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                if (X == Y && u == 1 && v == 0) continue;
+                const int br = 2 * X + u, bc = 2 * Y + v;
+                unsigned long long* const B0 = Bk + cl * 2 * half + (X == Y && u == v ? 0 : half);
+                auto wrap = [L](int d) { return d < 0 ? d + L : (d >= L ? d - L : d); };
+                unsigned long long *bx[4], *by[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int dx = wrap(4 * (br / nb8 - bc / nb8) + j - (i & 3));
+                    const int dy = wrap(8 * (br % nb8 - bc % nb8) + 2 * j + h - (i >> 2));
+                    bx[j] = B0 + (dx * ncopy + ((i >> 2) & (ncopy - 1))) * PT;
+                    by[j] = B0 + ((L + dy) * ncopy + (((i & 3) + 4 * h) & (ncopy - 1))) * PT;
+                }
+                int p = 0;
+#pragma unroll
+                for (int a = 0; a < RR; ++a)
+#pragma unroll
+                    for (int b = a + 1; b < RR; ++b, ++p) {
+                        const int(&A)[8] = pk[a][u][v];
+                        const int(&B)[8] = pk[b][u][v];
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)
+                            atomicAdd(by[g] + p, (unsigned long long)(long long)dot16(
+                                                     A[2 * g], B[2 * g], dot16(A[2 * g + 1], B[2 * g + 1], 0)));
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            int x = 0;
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) {
+                                const int t = 2 * g + (j >> 1);
+                                x = j & 1 ? mad_hi16(A[t], B[t], x) : mad_lo16(A[t], B[t], x);
+                            }
+                            atomicAdd(bx[j] + p, (unsigned long long)(long long)x);
+                        }
+                    }
+            }
+    }
+    __syncthreads();
+    // D[d] = F[d] + U[d] + U[-d]; sum Q^2 = sum_xy G^a_xy G^b_xy = sum_d D_x[d]
+    const int rl = 2 * L + 3;
+    for (int e = tid; e < ncl * PP * 2 * L; e += 64 * kGramWaves) {
+        const int cl = e / (PP * 2 * L), f = e % (PP * 2 * L), p = f / (2 * L), xd = f % (2 * L), d = xd % L;
+        const unsigned long long* const Fb = Bk + cl * 2 * half + p;
+        unsigned long long v = 0;
+        for (int k = 0; k < ncopy; ++k)
+            v += Fb[(xd * ncopy + k) * PT] + Fb[half + (xd * ncopy + k) * PT] +
+                 Fb[half + ((xd - d + (L - d) % L) * ncopy + k) * PT];
+        unsigned long long* const rp = (unsigned long long*)(sh.rec + ((size_t)(cfg0 + c0 + cl) * PP + p) * rl);
+        atomicAdd(rp + xd, v);
+        if (xd < L) {
+            atomicAdd(rp + 2 * L + 1, v);
+            atomicAdd(rp + 2 * L + 2, 0ull - 2 * kSqBias * v);  // what the overlap kernel's squares add too much
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The same for Ltau > 8192, int64 products.
+//
+// One workgroup takes one configuration at a time.  It first counts the
+// down spins n^r_x of every site row (popcount along tau) into LDS; then its
+// four waves share the tile pairs (X, Y), X <= Y, of the upper triangle,
+// each wave alone (no barrier inside a configuration), one wave per SIMD:
+// the 2 x 2 blocks of 32 x 32 of every replica's G^r = S S^T (2 x 1 above 4
+// replicas), accumulators in the AGPRs, K = tau in chunks of 64, the {0,1}
+// int8 operands built in registers from each lane's bit row.  The epilogue
+// forms G = Ltau - 2 (n_x + n_y) + 4 (B B^T)_xy and the products G^a G^b.
+//
+// BLK (L a multiple of 8): tile X holds the 8 x 8 block of sites
+// (bx, by) = (X mod L/8, X div L/8), row r the site (8bx + r mod 8,
+// 8by + r div 8).  The 16 elements of a lane then take 4 values of x1 - y1
+// (one per q mod 4) and 4 of x2 - y2 (one per q div 4), so each lane sums
+// them in registers and adds 8 bucket values per pair and block, not 32.
+// Otherwise tile X holds the slots 64X .. 64X + 63 and every element adds
+// its own two.
+// ---------------------------------------------------------------------------
+template <int RR, int NV, bool BLK>
 __global__ void __launch_bounds__(64 * kGramWaves)
-    __attribute__((amdgpu_waves_per_eu(gram_wpe(RR, NV, NARROW), gram_wpe(RR, NV, NARROW))))
-k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
-    static_assert(BLK || !NARROW, "the int32 epilogue takes the 8 x 8 site blocks");
+    __attribute__((amdgpu_waves_per_eu(1, 1)))
+k_gram_wide(ShapeDev sh, int cfg0, int ncfg) {
     constexpr int PP = RR * (RR - 1) / 2;
     extern __shared__ __align__(16) uint8_t smem[];
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nc = sh.nc, nxp = sh.nxp;
@@ -187,7 +409,7 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
     const int ntp = ntile * (ntile + 1) / 2;
     const int nbl = L >> 3;
     auto site = [&](int X, int r) {
-        if constexpr (BLK) return (8 * (X / nbl) + (r >> 3)) * L + 8 * (X % nbl) + (r & 7);
+        if constexpr (BLK) return site_slot(L, 8 * (X % nbl) + (r & 7), 8 * (X / nbl) + (r >> 3));
         return 64 * X + r;
     };
     for (int e = tid; e < 2 * PP * 2 * L; e += 64 * kGramWaves) Fb[e] = 0;  // F and U
@@ -211,9 +433,7 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
             int sb[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) sb[v] = site(Y, 32 * (v0 + v) + i);
-            // NARROW: fp32 accumulators of the fp4 form (below), else int32
-            using Acc = std::conditional_t<NARROW, v16f, v16i>;
-            Acc acc[RR][2][NV];
+            v16i acc[RR][2][NV];
 #pragma unroll
             for (int r = 0; r < RR; ++r)
 #pragma unroll
@@ -222,57 +442,6 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
                     for (int v = 0; v < NV; ++v)
 #pragma unroll
                         for (int q = 0; q < 16; ++q) acc[r][u][v][q] = 0;
-            // The fp4 K loop: 64 values of tau per MFMA.  Lane (i, h) feeds
-            // row i with the 32 bits of half h of its chunk word, element
-            // 8m + j (register m, nibble j) being bit 4j + m, as the e2m1
-            // values 0 and 0.5 (nibble 0 or 1: one mask per register).  The
-            // row side's block scale 2^4 makes each coincidence add 4, so the
-            // accumulator holds 4 (B B^T), exact in fp32 (at most 4 Ltau).
-            auto kloop4 = [&](auto diagC) {
-                constexpr bool kDiag = decltype(diagC)::value;
-                constexpr int NB = kDiag ? 0 : NV;
-                const uint32_t* const pt32 = (const uint32_t*)pt;
-                auto fetch = [&](int c, uint32_t (&wa)[2][RR], uint32_t (&wb)[NV][RR]) {
-#pragma unroll
-                    for (int r = 0; r < RR; ++r) {
-                        const size_t o = ((size_t)r * nc + c) * nxp;
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) wa[u][r] = pt32[2 * (o + sa[u]) + h];
-#pragma unroll
-                        for (int v = 0; v < NB; ++v) wb[v][r] = pt32[2 * (o + sb[v]) + h];
-                    }
-                };
-                auto chunk = [&](const uint32_t (&wa)[2][RR], const uint32_t (&wb)[NV][RR]) {
-                    i32x8 A[2][RR], B[NV][RR];
-#pragma unroll
-                    for (int r = 0; r < RR; ++r) {
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) A[u][r] = fp4_bits_operand(wa[u][r]);
-#pragma unroll
-                        for (int v = 0; v < NB; ++v) B[v][r] = fp4_bits_operand(wb[v][r]);
-                    }
-#pragma unroll
-                    for (int r = 0; r < RR; ++r)
-#pragma unroll
-                        for (int u = 0; u < 2; ++u)
-#pragma unroll
-                            for (int v = 0; v < NV; ++v) {
-                                if (kDiag && NV == 2 && u == 1 && v == 0) continue;
-                                const i32x8 b = kDiag ? A[NV == 2 ? v : v0][r] : B[v][r];
-                                acc[r][u][v] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                                    A[u][r], b, acc[r][u][v], kFp4, kFp4, 0, kScaleRow, 0, kScaleOne);
-                            }
-                };
-                uint32_t w0a[2][RR], w0b[NV][RR], w1a[2][RR], w1b[NV][RR];
-                fetch(0, w0a, w0b);
-                for (int c = 0; c + 1 < nc; c += 2) {
-                    fetch(c + 1, w1a, w1b);
-                    chunk(w0a, w0b);
-                    fetch(min(c + 2, nc - 1), w0a, w0b);
-                    chunk(w1a, w1b);
-                }
-                if (nc & 1) chunk(w0a, w0b);
-            };
             // the K loop; kDiag: Y = X, the column rows are row rows (no
             // loads of their own) and, with both column blocks, the block
             // (1, 0) is skipped
@@ -333,77 +502,8 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
             // at a branch join)
             auto finish = [&](auto diagC) {
             constexpr bool diag = decltype(diagC)::value;
-            if constexpr (NARROW)
-                kloop4(diagC);
-            else
-                kloop(diagC);
+            kloop(diagC);
             // epilogue, block by block
-            if constexpr (NARROW) {
-                // |G| <= Ltau <= 8192: a product is below 2^26 and a sum of
-                // 16 of them below 2^30, so both are formed in int32 with
-                // 24-bit multiplies.  The x1 - y1 buckets of a lane are the
-                // same in every block of the tile, so an off-diagonal pair
-                // sums them over its blocks and flushes them once.
-                const int x1 = 8 * (X % nbl) + 4 * h, y1 = 8 * (Y % nbl) + (i & 7);
-                int sxa[PP][4];
-#pragma unroll
-                for (int p = 0; p < PP; ++p)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) sxa[p][j] = 0;
-                auto flush_x = [&](unsigned long long* Db) {
-#pragma unroll
-                    for (int p = 0; p < PP; ++p)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            atomicAdd(&Db[(p * 2 + 0) * L + (x1 + j - y1 + L) % L],
-                                      (unsigned long long)(long long)sxa[p][j]);
-                            sxa[p][j] = 0;
-                        }
-                };
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    int rn[RR][16];  // 2 n^r of the rows of this lane's elements
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        const int xs = site(X, 32 * u + 8 * (q >> 2) + 4 * h + (q & 3));
-#pragma unroll
-                        for (int r = 0; r < RR; ++r) rn[r][q] = 2 * nS[r * nxp + xs];
-                    }
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        const int V = v0 + v;
-                        if (diag && NV == 2 && u == 1 && V == 0) continue;
-                        unsigned long long* Db = (diag && (NV == 1 || u == V)) ? Fb : Ub;
-                        const int x2 = 8 * (X / nbl) + 4 * u, y2 = 8 * (Y / nbl) + ((32 * V + i) >> 3);
-                        int G[RR][16];
-#pragma unroll
-                        for (int r = 0; r < RR; ++r) {
-                            const int nb = Lt - 2 * nS[r * nxp + sb[v]];
-#pragma unroll
-                            for (int q = 0; q < 16; ++q) G[r][q] = nb - rn[r][q] + (int)acc[r][u][v][q];
-                        }
-                        int p = 0;
-#pragma unroll
-                        for (int a = 0; a < RR; ++a)
-#pragma unroll
-                            for (int b = a + 1; b < RR; ++b, ++p) {
-                                int sy[4] = {0, 0, 0, 0};
-#pragma unroll
-                                for (int q = 0; q < 16; ++q) {
-                                    const int hv = __mul24(G[a][q], G[b][q]);
-                                    sxa[p][q & 3] += hv;
-                                    sy[q >> 2] += hv;
-                                }
-#pragma unroll
-                                for (int j = 0; j < 4; ++j)
-                                    atomicAdd(&Db[(p * 2 + 1) * L + (x2 + j - y2 + L) % L],
-                                              (unsigned long long)(long long)sy[j]);
-                            }
-                        if (diag) flush_x(Db);
-                    }
-                }
-                if (!diag) flush_x(Ub);
-            } else
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -460,7 +560,10 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg) {
                             if (x >= L2 || y >= L2) continue;
                             int G[RR];
                             gram(q, G);
-                            const int dx = (x % L - y % L + L) % L, dy = (x / L - y / L + L) % L;
+                            int x1, x2, y1, y2;
+                            slot_site(L, x, x1, x2);
+                            slot_site(L, y, y1, y2);
+                            const int dx = (x1 - y1 + L) % L, dy = (x2 - y2 + L) % L;
                             int p = 0;
 #pragma unroll
                             for (int a = 0; a < RR; ++a)
@@ -692,12 +795,13 @@ __global__ void __launch_bounds__(256) k_gram_plain(ShapeDev sh, int cfg) {
     const long long el = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (el < (long long)L2 * L2) {
         const int x = (int)(el / L2), y = (int)(el % L2);
+        const int sx = site_slot(L, x % L, x / L), sy = site_slot(L, y % L, y / L);
         int G[kMaxR];
         for (int r = 0; r < R; ++r) {
             const size_t m = (size_t)cfg * R + r;
             int acc = 0;
             for (int c = 0; c < sh.nc; ++c)
-                acc += dot64(sh.Pt[(m * sh.nc + c) * sh.nxp + x], sh.Pt[(m * sh.nc + c) * sh.nxp + y],
+                acc += dot64(sh.Pt[(m * sh.nc + c) * sh.nxp + sx], sh.Pt[(m * sh.nc + c) * sh.nxp + sy],
                              min(64, sh.Lt - 64 * c));
             G[r] = acc;
         }
@@ -755,9 +859,10 @@ __global__ void k_dump(ShapeDev sh, int cfg, int a, int b) {
             const int r = e < n1 ? a : b;
             const long long f = e % n1;
             const int x = (int)(f / L2), y = (int)(f % L2);
+            const int sx = site_slot(sh.L, x % sh.L, x / sh.L), sy = site_slot(sh.L, y % sh.L, y / sh.L);
             const size_t m = (size_t)cfg * R + r;
             for (int c = 0; c < sh.nc; ++c)
-                acc += dot64(sh.Pt[(m * sh.nc + c) * sh.nxp + x], sh.Pt[(m * sh.nc + c) * sh.nxp + y],
+                acc += dot64(sh.Pt[(m * sh.nc + c) * sh.nxp + sx], sh.Pt[(m * sh.nc + c) * sh.nxp + sy],
                              min(64, Lt - 64 * c));
         } else {
             const long long f = e - 2 * n1;
@@ -784,7 +889,7 @@ __global__ void k_buckets(ShapeDev sh) {
     }
 }
 
-size_t gram_lds(int RR, int L) {
+size_t gram_wide_lds(int RR, int L) {
     const int PP = RR * (RR - 1) / 2;
     const int nxp = 64 * ((L * L + 63) / 64);
     return (size_t)2 * PP * 2 * L * 8 + (size_t)RR * nxp * 4;
@@ -796,7 +901,7 @@ hipError_t launch_overlap_nx(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hi
     static bool lds_set = false;
     if (!lds_set) {
         const hipError_t e = hipFuncSetAttribute((const void*)k_overlap_mfma<NU, NX>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 16 * NU * 64 * 16);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
         if (e != hipSuccess) return e;
         lds_set = true;
     }
@@ -825,43 +930,67 @@ hipError_t launch_overlap(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipSt
 }
 
 template <int RR>
-hipError_t launch_mfma(const ShapeDev& sh, int cfg0, int ncfg, hipStream_t st) {
-    int dev = 0, ncu = 256;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    // a wave holds every replica's G of its unit: 64 x 64 up to 4 replicas,
-    // 64 x 32 above; with the int32 epilogue and more configurations than
-    // CUs two waves share a SIMD, each with at most 128 accumulators (64 x 64
-    // for 2 replicas, else 64 x 32)
-    constexpr int NV = RR <= 4 ? 2 : 1;
-    constexpr int NVn = RR <= 2 ? 2 : 1;
+hipError_t launch_gram(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStream_t st) {
+    constexpr int PP = RR * (RR - 1) / 2;
+    // tiles per configuration: four, two or one configuration at a time give
+    // each of the four waves a tile (L <= 8: one tile, L <= 16: 6 or 10)
+    const int nblk = ((sh.L + 3) / 4) * ((sh.L + 7) / 8), ntile = (nblk + 1) / 2, ntp = ntile * (ntile + 1) / 2;
+    int ncw = ntp == 1 ? 4 : (ntp <= 10 ? 2 : 1);
+    while (ncw > 1 && (ncfg + ncw - 1) / ncw < 2 * ncu) ncw /= 2;
+    const int nitem = (ncfg + ncw - 1) / ncw;
+    const bool grouped = ncu % 8 == 0 && nitem >= 128;
+    // from 36 tiles (L >= 18) three workgroups share a configuration: the
+    // rows are read by as many fewer configurations at a time through an
+    // L2 (L = 24: 907 -> 876 us; L = 12 with its 6 tiles 172 -> 198)
+    int nsplit = ntp >= 36 ? 3 : 1;
+    while (nitem * nsplit < 2 * ncu && kGramWaves * nsplit < ncw * ntp) nsplit *= 2;
+    // copies of the buckets: 8, or 4 where 8 would not leave room for two
+    // workgroups on a CU
+    const size_t one = (size_t)ncw * 4 * sh.L * gram_pitch(PP) * 8;
+    const int ncopy = 8 * one <= 72 * 1024 ? 8 : 4;
     static bool lds_set = false;
     if (!lds_set) {
-        for (const void* f : {(const void*)k_gram_mfma<RR, NVn, true, true>, (const void*)k_gram_mfma<RR, NV, true, true>,
-                              (const void*)k_gram_mfma<RR, NV, true, false>, (const void*)k_gram_mfma<RR, NV, false, false>}) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_gram_mfma<RR>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+        if (e != hipSuccess) return e;
+        lds_set = true;
+    }
+    hipLaunchKernelGGL(k_gram_mfma<RR>, dim3((unsigned)((grouped ? (nitem + 7) / 8 * 8 : nitem) * nsplit)),
+                       dim3(64 * kGramWaves), ncopy * one, st, sh, cfg0, ncfg, ncw, nsplit, ncopy, (int)grouped);
+    return hipGetLastError();
+}
+
+template <int RR>
+hipError_t launch_gram_wide(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStream_t st) {
+    // a wave holds every replica's G of its unit: 64 x 64 up to 4 replicas,
+    // 64 x 32 above
+    constexpr int NV = RR <= 4 ? 2 : 1;
+    static bool lds_set = false;
+    if (!lds_set) {
+        for (const void* f : {(const void*)k_gram_wide<RR, NV, true>, (const void*)k_gram_wide<RR, NV, false>}) {
             const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)gram_lds(RR, 32));
+                                                     (int)gram_wide_lds(RR, 32));
             if (e != hipSuccess) return e;
         }
         lds_set = true;
     }
-    const int ggrid = std::min(ncfg, ncu);
-    auto narrow = [&](auto nvC) {
-        constexpr int nv = decltype(nvC)::value;
-        hipLaunchKernelGGL((k_gram_mfma<RR, nv, true, true>), dim3(std::min(ncfg, gram_wpe(RR, nv, true) * ncu)),
-                           dim3(64 * kGramWaves), gram_lds(RR, sh.L), st, sh, cfg0, ncfg);
-    };
-    if (sh.L % 8 == 0 && sh.Lt <= kNarrowLt && ncfg > ncu)
-        narrow(std::integral_constant<int, NVn>{});
-    else if (sh.L % 8 == 0 && sh.Lt <= kNarrowLt)
-        narrow(std::integral_constant<int, NV>{});
-    else if (sh.L % 8 == 0)
-        hipLaunchKernelGGL((k_gram_mfma<RR, NV, true, false>), dim3(ggrid), dim3(64 * kGramWaves), gram_lds(RR, sh.L),
-                           st, sh, cfg0, ncfg);
+    const int grid = std::min(ncfg, ncu);
+    if (sh.L % 8 == 0)
+        hipLaunchKernelGGL((k_gram_wide<RR, NV, true>), dim3(grid), dim3(64 * kGramWaves), gram_wide_lds(RR, sh.L), st,
+                           sh, cfg0, ncfg);
     else
-        hipLaunchKernelGGL((k_gram_mfma<RR, NV, false, false>), dim3(ggrid), dim3(64 * kGramWaves),
-                           gram_lds(RR, sh.L), st, sh, cfg0, ncfg);
-    const hipError_t e = hipGetLastError();
+        hipLaunchKernelGGL((k_gram_wide<RR, NV, false>), dim3(grid), dim3(64 * kGramWaves), gram_wide_lds(RR, sh.L), st,
+                           sh, cfg0, ncfg);
+    return hipGetLastError();
+}
+
+template <int RR>
+hipError_t launch_mfma(const ShapeDev& sh, int cfg0, int ncfg, hipStream_t st) {
+    int dev = 0, ncu = 256;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    const hipError_t e = sh.Lt <= kNarrowLt ? launch_gram<RR>(sh, cfg0, ncfg, ncu, st)
+                                            : launch_gram_wide<RR>(sh, cfg0, ncfg, ncu, st);
     if (e != hipSuccess) return e;
     return launch_overlap(sh, cfg0, ncfg, ncu, st);
 }
@@ -873,7 +1002,7 @@ bool measure_ok(const ShapeDev& sh) { return sh.R >= 2 && sh.R <= kMaxR && sh.L 
 
 hipError_t launch_transpose(const ShapeDev& sh, hipStream_t st) {
     const long long items = (long long)sh.R * sh.nk * sh.W * sh.nc * sh.nx;
-    const int grid = (int)std::min<long long>(items, 8192);
+    const int grid = (int)std::min<long long>((items + 7) / 8 * 8, 8192);
     static bool lds_set = false;  // above 64 KiB of LDS per workgroup
     if (!lds_set) {
         const hipError_t e = hipFuncSetAttribute((const void*)k_transpose,

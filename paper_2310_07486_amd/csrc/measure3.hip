@@ -84,10 +84,10 @@ k_gram_store(ShapeDev sh, int cfg0, int ncfg, int nb, int8_t* __restrict__ ws) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int i = lane & 31, h5 = lane >> 5, sh4 = 4 * h5;
     const int ntp = nt * (nt + 1) / 2;
-    // site of slot rho of tile T, -1 on padding
+    // layout slot of slot rho of tile T, -1 on padding
     auto site = [&](int T, int rho) {
         const int x1 = 8 * (T % nb) + slot_d1(rho), x2 = 8 * (T / nb) + slot_d2(rho);
-        return (x1 < L && x2 < L) ? x1 + L * x2 : -1;
+        return (x1 < L && x2 < L) ? site_slot(L, x1, x2) : -1;
     };
     for (int cl = blockIdx.x; cl < ncfg; cl += gridDim.x) {
         const uint64_t* const pt = sh.Pt + (size_t)(cfg0 + cl) * RR * nc * nxp;

@@ -38,9 +38,10 @@ struct ShapeDev {
     // Measurement layouts (one bit per spin, one row per sample), written by
     // the transpose kernel for configuration m = (i*S + s)*R + r (k-index i,
     // sample s, replica r):
-    //   Pt[(m*nc + c)*nxp + xy]  bit t = spin bit of (tau = 64c + t, xy)
-    //   Px[(m*nx + g)*Lt + tau]  bit t = spin bit of (tau, xy = 64g + t)
-    // nc = ceil(Lt/64), nx = ceil(L2/64), nxp = 64*nx; padding bits are 0.
+    //   Pt[(m*nc + c)*nxp + slot]  bit t = spin bit of (tau = 64c + t, slot)
+    //   Px[(m*nx + g)*Lt + tau]    bit t = spin bit of (tau, slot = 64g + t)
+    // slot: the site order of site_slot below.  nc = ceil(Lt/64),
+    // nx = ceil(L2/64), nxp = 64*nx; padding bits are 0.
     uint64_t* Pt;
     uint64_t* Px;
     int32_t* dump;  // [2*L2*L2 + Lt*Lt] debug matrices
@@ -187,6 +188,19 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // One unscaled v_mfma_f32_32x32x64_f8f6f4 on fp4 operands: 64 values of K.
 __device__ __forceinline__ f32x16 mfma_fp4(i32x8 a, i32x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, kFp4, kFp4, 0, 0, 0, 0);
+}
+
+// Site order of the measurement layouts: strips of four x1 (the last one of
+// two where L is not a multiple of 4), x2 running along a strip.  A block of 4
+// x1 by 8 x2 sites, the rows of one MFMA operand, is then 32 consecutive slots.
+__host__ __device__ inline int site_slot(int L, int x1, int x2) {
+    const int a = x1 >> 2, w = L - 4 * a < 4 ? 2 : 4;
+    return 4 * L * a + w * x2 + (x1 & 3);
+}
+__host__ __device__ inline void slot_site(int L, int slot, int& x1, int& x2) {
+    const int a = slot / (4 * L), rem = slot - 4 * L * a, two = L - 4 * a < 4;
+    x2 = two ? rem >> 1 : rem >> 2;
+    x1 = 4 * a + (two ? rem & 1 : rem & 3);
 }
 
 // Sixteen int8 bytes summing to v, |v| <= 1792: fifteen of floor(v / 16) and
