@@ -643,7 +643,9 @@ template <int NU, int NX>
 __global__ void __launch_bounds__(64 * kOverlapWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_overlap_mfma(ShapeDev sh, int cfg0, int ncfg, int npanel, int nsplit, int grouped) {
     extern __shared__ __align__(16) uint8_t smem[];
-    i32x4* const Aop = (i32x4*)smem;  // [nx][NU][64]
+    i32x4* const Aop = (i32x4*)smem;                                        // [nx][NU][64]
+    unsigned long long* const S4 = (unsigned long long*)(Aop + sh.nx * NU * 64);  // [P][64], a slot per lane
+    int* const Tr = (int*)(S4 + 64 * sh.P);                                 // [P][64]
     const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L2 = sh.L2, Lt = sh.Lt, nx = sh.nx, R = sh.R, P = sh.P;
@@ -666,6 +668,34 @@ k_overlap_mfma(ShapeDev sh, int cfg0, int ncfg, int npanel, int nsplit, int grou
         const __amdgpu_buffer_rsrc_t words = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(((uint64_t)base_hi << 32) | base_lo), (short)0, R * nx * Lt * 8, 0x00020000);
         const int voff = 8 * i + 4 * h;
+        for (int e = tid; e < 64 * P; e += 64 * kOverlapWaves) {
+            S4[e] = 0;
+            Tr[e] = 0;
+        }
+        __syncthreads();
+        if (part == 0) {
+            // trQ = sum over the panel's rows of L^2 - 2 popcount(a ^ b)
+            int tr[kMaxP] = {};
+            for (int e = tid; e < nx * NU * 32; e += 64 * kOverlapWaves) {
+                const int g = e / (NU * 32), row = row0 + e % (NU * 32);
+                if (row >= Lt) continue;
+                uint64_t w[kMaxR];
+#pragma unroll
+                for (int r = 0; r < kMaxR; ++r) w[r] = r < R ? px[((size_t)r * nx + g) * Lt + row] : 0ull;
+                int q = 0;
+#pragma unroll
+                for (int a = 0; a < kMaxR; ++a)
+#pragma unroll
+                    for (int b = a + 1; b < kMaxR; ++b, ++q)
+                        if (b < R) tr[q] += (g == 0 ? L2 : 0) - 2 * (int)__popcll(w[a] ^ w[b]);
+            }
+            int q = 0, k6 = 0;
+#pragma unroll
+            for (int a = 0; a < kMaxR; ++a)
+#pragma unroll
+                for (int b = a + 1; b < kMaxR; ++b, ++k6)
+                    if (b < R) atomicAdd(&Tr[64 * q++ + lane], tr[k6]);
+        }
         int p = 0;
         for (int a = 0; a + 1 < R; ++a) {
             __syncthreads();  // the waves have read the previous panel
@@ -684,15 +714,6 @@ k_overlap_mfma(ShapeDev sh, int cfg0, int ncfg, int npanel, int nsplit, int grou
             __syncthreads();
             for (int b = a + 1; b < R; ++b, ++p) {
                 unsigned long long s4 = 0;
-                int tr = 0;
-                if (part == 0) {
-                    for (int e = tid; e < nx * NU * 32; e += 64 * kOverlapWaves) {
-                        const int g = e / (NU * 32), row = row0 + e % (NU * 32);
-                        if (row < Lt)
-                            tr += (g == 0 ? L2 : 0) - 2 * (int)__popcll(px[((size_t)a * nx + g) * Lt + row] ^
-                                                                         px[((size_t)b * nx + g) * Lt + row]);
-                    }
-                }
                 const int step = kOverlapWaves * nsplit;
                 // the words of chunk g of tile t (kept below the last tile, so
                 // that the scalar offset stays inside the descriptor and rows
@@ -760,16 +781,22 @@ k_overlap_mfma(ShapeDev sh, int cfg0, int ncfg, int npanel, int nsplit, int grou
                             }
                     s4 -= (unsigned long long)(NU * 32) * kSqBias * kSqBias;
                 }
+                atomicAdd(&S4[64 * p + lane], s4);
+            }
+        }
+        __syncthreads();
+        for (int q = wv; q < P; q += kOverlapWaves) {
+            unsigned long long v = S4[64 * q + lane];
+            int tr = Tr[64 * q + lane];
 #pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    s4 += (unsigned long long)__shfl_xor((long long)s4, off, 64);
-                    tr += __shfl_xor(tr, off, 64);
-                }
-                if (lane == 0) {
-                    unsigned long long* rp = (unsigned long long*)(sh.rec + ((size_t)cfg * P + p) * rl);
-                    if (part == 0) atomicAdd(rp + 2 * sh.L, (unsigned long long)(long long)tr);
-                    atomicAdd(rp + 2 * sh.L + 2, s4);
-                }
+            for (int off = 32; off > 0; off >>= 1) {
+                v += (unsigned long long)__shfl_xor((long long)v, off, 64);
+                tr += __shfl_xor(tr, off, 64);
+            }
+            if (lane == 0) {
+                unsigned long long* rp = (unsigned long long*)(sh.rec + ((size_t)cfg * P + q) * rl);
+                if (part == 0) atomicAdd(rp + 2 * sh.L, (unsigned long long)(long long)tr);
+                atomicAdd(rp + 2 * sh.L + 2, v);
             }
         }
     }
@@ -911,7 +938,8 @@ hipError_t launch_overlap_nx(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hi
     const bool grouped = ncu % 8 == 0 && ncfg >= 128;
     const long long items = (long long)ncfg * npanel * nsplit;
     const long long grid = grouped ? (long long)((ncfg + 7) / 8) * 8 * npanel * nsplit : items;
-    hipLaunchKernelGGL((k_overlap_mfma<NU, NX>), dim3((unsigned)grid), dim3(64 * kOverlapWaves), (size_t)sh.nx * NU * 64 * 16, st, sh,
+    hipLaunchKernelGGL((k_overlap_mfma<NU, NX>), dim3((unsigned)grid), dim3(64 * kOverlapWaves),
+                       (size_t)sh.nx * NU * 64 * 16 + (size_t)64 * sh.P * 12, st, sh,
                        cfg0, ncfg, npanel, nsplit, (int)grouped);
     return hipGetLastError();
 }
