@@ -1,4 +1,4 @@
-// Two-time correlations on int8 MFMA.
+// Two-time correlations on fp4 MFMA.
 //
 // Paper: arXiv:2310.07486, Methods, "Two-times observables": C_A(tau) is the
 // average over tau1 of A(S_tau1) A(S_tau1+tau) along the periodic time
@@ -8,240 +8,239 @@
 // Both come from the time Gram of one replica, H = S^T S (Ltau x Ltau,
 // H_t1t2 = sum_x S_x,t1 S_x,t2, |H| <= L^2):
 //   c[d]  = sum_t1 H_t1,(t1+d) mod Ltau,   q2[d] = sum_t1 H_t1,(t1+d) mod Ltau ^ 2,
-// summed over the replicas of the configuration.  With B = (1 - S)/2,
-// H = L^2 - 2 (m_t1 + m_t2) + 4 (B^T B), so the contraction over sites runs on
-// int8 operands (v_mfma_i32_32x32x32_i8) built in registers from the bit
-// rows along xy, as in the replica overlap, with the rank-one corrections in
-// one more K step so that the accumulator is H itself.
+// summed over the replicas of the configuration.  The contraction over sites
+// runs on fp4 MFMAs with +-1 operands built in registers from the bit rows
+// along the sites (7 VALU per operand, one operand per MFMA); the fp32
+// accumulator is H itself, exactly.
 //
-// One workgroup takes one configuration at a time; its four waves share the
-// upper triangle of 64 x 64 tiles (each wave alone, no barrier inside a
-// configuration) and take the replicas two at a time.  Each element with
-// t1 <= t2 adds sum_r H^r and sum_r (H^r)^2 to the LDS buckets U of its
-// diagonal d = t2 - t1: for element q of a 32 x 32 block all lanes of a
-// half-wave sit at the same row offset r_q, so rotating the lanes by r_q
-// (ds_bpermute) brings the elements of one diagonal into one lane, which
-// sums them and adds two values per block (d >= 0 and d - 32) instead of
-// one per element.  H is symmetric, so the record is
-// c[d] = U[d] + U[Ltau - d] (c[0] = U[0]), stored once per configuration.
+// The waves of a workgroup share the upper triangle of 64 x 64 tiles of one
+// configuration, each wave alone, the replicas in turn: sum_r H^r and
+// sum_r (H^r)^2 of the tile's elements stay in registers (exact in fp32: below
+// 2^23), two instructions per element and replica.  Then every element adds
+// its two sums to the LDS buckets of its diagonal d = t2 - t1: in the MFMA
+// layout the lanes of a half-wave hold 32 consecutive diagonals for each
+// element q, at a fixed offset from q to q, so an addition is one LDS
+// instruction without conflicts (a copy of the buckets per half-wave) and no
+// address arithmetic.  Elements below the diagonal fall into 64 slots that
+// nobody reads.  c fits 32 bits; q2 too while R L^4 Ltau < 2^32, else kWide
+// keeps it in 64.  H is symmetric, so the record is c[d] = U[d] + U[Ltau - d]
+// (c[0] = U[0]).
+//
+// Bound by the operand VALU (the matrix cores would allow two thirds of the
+// time).  L = 24, Ltau = 2048, 4 replicas, 512 configurations: 3.60 ms with int8
+// MFMAs, a correction step, two replicas at a time and the diagonals gathered
+// by ds_bpermute -> 1.51 ms.
 #include <algorithm>
+#include <type_traits>
 
 #include "tfim_internal.h"
 
 namespace tfim {
 namespace {
 
-typedef int v16i __attribute__((ext_vector_type(16)));
-
 constexpr int kMaxLtTime = 4096;
 constexpr int kTcWaves = 4;  // waves per workgroup
+constexpr int kDrop = 64;    // slots of the elements below the diagonal
 
-template <int RR>
-__global__ void __launch_bounds__(64 * kTcWaves) __attribute__((amdgpu_waves_per_eu(2))) k_timecorr_mfma(ShapeDev sh, int cfg0, int ncfg,
-                                                                int64_t* __restrict__ rec) {
-    extern __shared__ unsigned long long Cb[];  // [2][Lt]: c, q2
-    const int L2 = sh.L2, Lt = sh.Lt, nx = sh.nx;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int i = lane & 31, h = lane >> 5, sh4 = 4 * h;
-    const int ntt = (Lt + 63) / 64;
-    const int ntp = ntt * (ntt + 1) / 2;
-    const int h2 = L2 >> 1;
-    for (int e = tid; e < 2 * Lt; e += 64 * kTcWaves) Cb[e] = 0;
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+// Buckets of one half-wave's copy, slot d + kDrop.
+__host__ __device__ constexpr int tc_slots(int Lt) { return 64 * ((Lt + 63) / 64) + kDrop; }
+
+template <bool kOdd, bool kWide>
+__global__ void __launch_bounds__(64 * kTcWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_timecorr_mfma(ShapeDev sh, int cfg0, int ncfg, int nsplit, int grouped, int64_t* __restrict__ rec) {
+    using Q = std::conditional_t<kWide, unsigned long long, uint32_t>;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int L2 = sh.L2, Lt = sh.Lt, nx = sh.nx, R = sh.R, ns = tc_slots(Lt);
+    Q* const q2b = (Q*)smem;                      // [2][ns]
+    uint32_t* const cb = (uint32_t*)(q2b + 2 * ns);  // [2][ns]
+    const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ntt = (Lt + 63) / 64, ntp = ntt * (ntt + 1) / 2;
+    // grouped: workgroup b runs on XCD b mod 8, which takes the configurations
+    // b mod 8, b mod 8 + 8, ..., so that the nsplit workgroups of one read its
+    // rows through one L2
+    const int ng = grouped ? 8 : 1, item = (int)blockIdx.x / ng;
+    const int cl = item / nsplit * ng + (grouped ? (int)blockIdx.x & 7 : 0), part = item % nsplit;
+    if (cl >= ncfg) return;
+    for (int e = tid; e < 2 * ns; e += 64 * kTcWaves) {
+        q2b[e] = 0;
+        cb[e] = 0;
+    }
     __syncthreads();
-    for (int cl = blockIdx.x; cl < ncfg; cl += gridDim.x) {
-        const uint64_t* const px = sh.Px + (size_t)(cfg0 + cl) * RR * nx * Lt;
-        for (int tp = wv; tp < ntp; tp += kTcWaves) {
-            int T = 0, rem = tp;
-            while (rem >= ntt - T) { rem -= ntt - T; ++T; }
-            const int T2 = T + rem;
-            // rows clamped into [0, Lt): a row past Lt only feeds elements
-            // the epilogue drops
-            const int ta0 = 64 * T + i, tb0 = 64 * T2 + i;
-            const int rowa[2] = {min(ta0, Lt - 1), min(ta0 + 32, Lt - 1)};
-            const int rowb[2] = {min(tb0, Lt - 1), min(tb0 + 32, Lt - 1)};
-            const bool edge = 64 * (T2 + 1) > Lt;  // T <= T2
+    const uint64_t* const px = sh.Px + (size_t)(cfg0 + cl) * R * nx * Lt;
+    const uint32_t base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)px);
+    const uint32_t base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)px >> 32));
+    const __amdgpu_buffer_rsrc_t words = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(((uint64_t)base_hi << 32) | base_lo), (short)0, R * nx * Lt * 8, 0x00020000);
+    // the last chunk's bits past L^2 cancel: half of them are turned over on
+    // the row side (their number is a multiple of 4)
+    const int padn = (64 * nx - L2) >> 1;
+    const uint64_t pad64 = padn ? ~0ull << (64 - padn) : 0ull;
+    for (int tp = part * kTcWaves + wv; tp < ntp; tp += kTcWaves * nsplit) {
+        int T = 0, rem = tp;
+        while (rem >= ntt - T) { rem -= ntt - T; ++T; }
+        const int T2 = T + rem;
+        int row[4];       // byte offsets of this lane's rows (t1), then columns (t2)
+        uint32_t mag[4];  // 0 past Ltau
 #pragma unroll
-            for (int r0 = 0; r0 < RR; r0 += 2) {
-                constexpr int kG = 2;
-                const int ng = min(kG, RR - r0);  // replicas of this group (uniform)
-                auto fetch = [&](int g, uint64_t (&wa)[2][kG], uint64_t (&wb)[2][kG]) {
+        for (int k = 0; k < 4; ++k) {
+            const int t = 64 * (k < 2 ? T : T2) + 32 * (k & 1) + i;
+            row[k] = 8 * min(t, Lt - 1);
+            mag[k] = t < Lt ? 0x22222222u : 0u;
+        }
+        // Chunks in pairs: lane (i, h) loads the whole word of chunk 2g + h,
+        // whose halves feed two MFMAs.  First comes an odd last chunk, by
+        // halves of its word, else the last pair (either holds the padding).
+        const int n = nx / 2, m = kOdd ? n : n - 1;  // pairs, and those after the first step
+        const uint32_t flip = (uint32_t)(pad64 >> (32 * h));
+        const uint64_t flip_pair = h ? pad64 : 0ull;
+        u32x2 w0[4], w1[4];
+        uint32_t wl[4];  // kOdd: the last chunk
+        auto fetch = [&](int r, int g, u32x2 (&w)[4]) {
+            const int so = (r * nx + 2 * g) * Lt * 8;
 #pragma unroll
-                    for (int u = 0; u < 2; ++u)
+            for (int k = 0; k < 4; ++k)
+                w[k] = __builtin_amdgcn_raw_buffer_load_b64(words, row[k] + h * Lt * 8, so, 0);
+        };
+        // the first loads of replica r
+        auto begin = [&](int r) {
+            if constexpr (kOdd) {
+                const int so = (r * nx + nx - 1) * Lt * 8;
 #pragma unroll
-                        for (int a = 0; a < kG; ++a) {
-                            const size_t m = (size_t)min(r0 + a, RR - 1) * nx + g;
-                            wa[u][a] = px[m * Lt + rowa[u]];
-                            wb[u][a] = px[m * Lt + rowb[u]];
-                        }
-                };
-                v16i acc[kG][2][2];
+                for (int k = 0; k < 4; ++k) wl[k] = __builtin_amdgcn_raw_buffer_load_b32(words, row[k] + 4 * h, so, 0);
+                if (n > 0) {
+                    fetch(r, 0, w0);
+                    fetch(r, min(1, n - 1), w1);
+                }
+            } else {
+                fetch(r, n - 1, w1);
+                fetch(r, 0, w0);
+            }
+        };
+        begin(0);
+        f32x16 hs[2][2] = {}, hq[2][2] = {};
+#pragma unroll 1
+        for (int r = 0; r < R; ++r) {
+            f32x16 acc[2][2];
+            auto step = [&](const uint32_t (&w)[4], auto firstC) {
+                constexpr bool kFirst = decltype(firstC)::value;
+                i32x4 o[4];
 #pragma unroll
-                for (int a = 0; a < kG; ++a)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int v = 0; v < 2; ++v)
-#pragma unroll
-                            for (int q = 0; q < 16; ++q) acc[a][u][v][q] = 0;
-                int ma[2][kG], mb[2][kG];
+                for (int k = 0; k < 4; ++k) o[k] = fp4_signs_operand(w[k], mag[k]);
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int a = 0; a < kG; ++a) ma[u][a] = mb[u][a] = 0;
-                auto chunk = [&](const uint64_t (&wa)[2][kG], const uint64_t (&wb)[2][kG]) {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int a = 0; a < kG; ++a) {
-                            ma[u][a] += __popcll(wa[u][a]);
-                            mb[u][a] += __popcll(wb[u][a]);
-                        }
-#pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) {
-                        i32x4 A[2][kG], B[2][kG];
-#pragma unroll
-                        for (int u = 0; u < 2; ++u)
-#pragma unroll
-                            for (int a = 0; a < kG; ++a) {
-                                A[u][a] = mfma_bits_operand<true>((uint32_t)(wa[u][a] >> (32 * ks)) >> sh4);
-                                B[u][a] = mfma_bits_operand<false>((uint32_t)(wb[u][a] >> (32 * ks)) >> sh4);
-                            }
-#pragma unroll
-                        for (int a = 0; a < kG; ++a)
-#pragma unroll
-                            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                                for (int v = 0; v < 2; ++v)
-                                    acc[a][u][v] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[u][a], B[v][a],
-                                                                                         acc[a][u][v], 0, 0, 0);
-                    }
-                };
-                // two word sets in turn, the next chunk in flight during this
-                // one; one straight loop block (a fetch past the last chunk
-                // reloads it) keeps the loads ahead and the waits exact
-                uint64_t w0a[2][kG], w0b[2][kG], w1a[2][kG], w1b[2][kG];
-                fetch(0, w0a, w0b);
-                for (int g = 0; g + 1 < nx; g += 2) {
-                    fetch(g + 1, w1a, w1b);
-                    chunk(w0a, w0b);
-                    fetch(min(g + 2, nx - 1), w0a, w0b);
-                    chunk(w1a, w1b);
-                }
-                if (nx & 1) chunk(w0a, w0b);
-                {  // H = 4 B^T B + X_t1 + Y_t2, X = h2 - 2 m_t1, Y = L^2 - h2 - 2 m_t2
-                    const i32x4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
-                    i32x4 A[2][kG], B[2][kG];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int a = 0; a < kG; ++a) {
-                            A[u][a] = h ? ones : mfma_pieces16(h2 - 2 * ma[u][a]);
-                            B[u][a] = h ? mfma_pieces16(L2 - h2 - 2 * mb[u][a]) : ones;
-                        }
-#pragma unroll
-                    for (int a = 0; a < kG; ++a)
-#pragma unroll
-                        for (int u = 0; u < 2; ++u)
-#pragma unroll
-                            for (int v = 0; v < 2; ++v)
-                                acc[a][u][v] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[u][a], B[v][a],
-                                                                                     acc[a][u][v], 0, 0, 0);
-                }
-                // epilogue: lane l gathers, for each q, the element of column
-                // (l + r_q) mod 32, which lies on diagonal l (or l - 32).
-                // kEdge: a tile that reaches past Ltau drops those elements
-                // (compiled apart, so the other tiles test nothing per
-                // element).
-                auto epilogue = [&](auto edgeC) {
-                    constexpr bool kEdge = decltype(edgeC)::value;
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int v = 0; v < 2; ++v) {
-                            const int D0 = 64 * (T2 - T) + 32 * (v - u);
-                            if (D0 + 31 < 0) continue;  // below the diagonal
-                            const int tau2 = 64 * T2 + 32 * v + i;
-                            // all of a lane's gathered values, and those of
-                            // diagonal l - 32 (i + r_q >= 32) apart
-                            int sA = 0, sN = 0, qA = 0, qN = 0;
-#pragma unroll
-                            for (int q = 0; q < 16; ++q) {
-                                const int r = 8 * (q >> 2) + 4 * h + (q & 3);
-                                int hs = 0, hq = 0;  // |H| <= L^2: a group's sums stay below 2^21
-#pragma unroll
-                                for (int a = 0; a < kG; ++a) {
-                                    if (a >= ng) continue;
-                                    const int Hv = acc[a][u][v][q];
-                                    hs += Hv;
-                                    hq += __mul24(Hv, Hv);
-                                }
-                                if constexpr (kEdge) {
-                                    const bool out = 64 * T + 32 * u + r >= Lt || tau2 >= Lt;
-                                    hs = out ? 0 : hs;
-                                    hq = out ? 0 : hq;
-                                }
-                                const int src = ((lane & 32) | ((lane + r) & 31)) << 2;
-                                const int gs = __builtin_amdgcn_ds_bpermute(src, hs);
-                                const int gq = __builtin_amdgcn_ds_bpermute(src, hq);
-                                const bool neg = i + r >= 32;
-                                sA += gs;
-                                qA += gq;
-                                sN += neg ? gs : 0;
-                                qN += neg ? gq : 0;
-                            }
-                            const int sP = sA - sN, qP = qA - qN;
-                            const int dP = D0 + i, dN = D0 + i - 32;
-                            if (dP >= 0 && dP < Lt) {
-                                atomicAdd(&Cb[dP], (unsigned long long)(long long)sP);
-                                atomicAdd(&Cb[Lt + dP], (unsigned long long)qP);
-                            }
-                            if (dN >= 0 && dN < Lt) {
-                                atomicAdd(&Cb[dN], (unsigned long long)(long long)sN);
-                                atomicAdd(&Cb[Lt + dN], (unsigned long long)qN);
-                            }
-                        }
-                };
-                if (edge)
-                    epilogue(std::true_type{});
-                else
-                    epilogue(std::false_type{});
+                    for (int v = 0; v < 2; ++v)
+                        acc[u][v] = mfma_fp4(fp4_wide(o[u]), fp4_wide(o[2 + v]), kFirst ? f32x16{} : acc[u][v]);
+            };
+            auto pair = [&](const u32x2 (&w)[4], auto firstC) {
+                constexpr bool kFirst = decltype(firstC)::value;
+                const uint64_t f = kFirst ? flip_pair : 0ull;
+                const uint32_t a[4] = {w[0][0] ^ (uint32_t)f, w[1][0] ^ (uint32_t)f, w[2][0], w[3][0]};
+                step(a, firstC);
+                const uint32_t b[4] = {w[0][1] ^ (uint32_t)(f >> 32), w[1][1] ^ (uint32_t)(f >> 32), w[2][1], w[3][1]};
+                step(b, std::false_type{});
+            };
+            if constexpr (kOdd) {
+                const uint32_t a[4] = {wl[0] ^ flip, wl[1] ^ flip, wl[2], wl[3]};
+                step(a, std::true_type{});
+            } else {
+                pair(w1, std::true_type{});
+                fetch(r, min(1, n - 1), w1);
             }
+            int g = 0;
+            for (; g + 1 < m; g += 2) {
+                pair(w0, std::false_type{});
+                fetch(r, min(g + 2, n - 1), w0);
+                pair(w1, std::false_type{});
+                fetch(r, min(g + 3, n - 1), w1);
+            }
+            if (g < m) pair(w0, std::false_type{});
+            begin(min(r + 1, R - 1));  // in flight during the sums below
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        const float H = acc[u][v][q];
+                        hs[u][v][q] += H;
+                        hq[u][v][q] = __builtin_fmaf(H, H, hq[u][v][q]);
+                    }
         }
-        __syncthreads();
-        // c[d] = U[d] + U[Ltau - d] for d > 0, c[0] = U[0] (likewise q2).  The
-        // terms of U[Ltau - d] cross the tau wrap: with an antiperiodic
-        // boundary they enter c with the sign -1 (q2 squares the sign away).
-        const bool anti = sh.apm != 0ull;
-        for (int e = tid; e < 2 * Lt; e += 64 * kTcWaves) {
-            const int hh = e / Lt, d = e % Lt;
-            const unsigned long long w = d ? Cb[hh * Lt + Lt - d] : 0ull;
-            const unsigned long long uu = (anti && hh == 0) ? Cb[e] - w : Cb[e] + w;
-            rec[(size_t)cl * 2 * Lt + e] = (int64_t)uu;
-        }
-        __syncthreads();
-        for (int e = tid; e < 2 * Lt; e += 64 * kTcWaves) Cb[e] = 0;
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                if (T == T2 && u == 1 && v == 0) continue;  // below the diagonal
+                // element q: slot + 27 - (8 (q div 4) + q mod 4)
+                const int slot = kDrop + 64 * (T2 - T) + 32 * (v - u) + i - 4 * h - 27 + h * ns;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const int off = 27 - 8 * (q >> 2) - (q & 3);
+                    atomicAdd(cb + slot + off, (uint32_t)(int)hs[u][v][q]);
+                    atomicAdd(q2b + slot + off, (Q)(uint32_t)hq[u][v][q]);
+                }
+            }
+    }
+    __syncthreads();
+    // c[d] = U[d] + U[Ltau - d] for d > 0, c[0] = U[0] (likewise q2).  The
+    // terms of U[Ltau - d] cross the tau wrap: with an antiperiodic boundary
+    // they enter c with the sign -1 (q2 squares the sign away).
+    const bool anti = sh.apm != 0ull;
+    int64_t* const out = rec + (size_t)cl * 2 * Lt;
+    for (int e = tid; e < 2 * Lt; e += 64 * kTcWaves) {
+        const int hh = e >= Lt, d = hh ? e - Lt : e;
+        auto U = [&](int k) -> int64_t {
+            const int s = kDrop + k;
+            return hh ? (int64_t)(q2b[s] + q2b[ns + s]) : (int64_t)(int32_t)(cb[s] + cb[ns + s]);
+        };
+        const int64_t w = d ? U(Lt - d) : 0;
+        const int64_t v = U(d) + (anti && !hh ? -w : w);
+        if (nsplit == 1)
+            out[e] = v;
+        else
+            atomicAdd((unsigned long long*)out + e, (unsigned long long)v);
     }
 }
 
-size_t timecorr_lds(int Lt) { return (size_t)2 * Lt * 8; }
+__global__ void k_zero_time(int64_t* __restrict__ rec, size_t n) {
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+        rec[i] = 0;
+}
 
-template <int RR>
-hipError_t launch_timecorr_rr(const ShapeDev& sh, int cfg0, int ncfg, int64_t* rec, hipStream_t st) {
+template <bool kOdd, bool kWide>
+hipError_t launch_timecorr_as(const ShapeDev& sh, int cfg0, int ncfg, int64_t* rec, hipStream_t st) {
     int dev = 0, ncu = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    const size_t lds = timecorr_lds(sh.Lt);
+    auto lds = [](int Lt) { return (size_t)2 * tc_slots(Lt) * (kWide ? 12 : 8); };
     static bool lds_set = false;  // above 64 KiB of LDS per workgroup
     if (!lds_set) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_timecorr_mfma<RR>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)timecorr_lds(kMaxLtTime));
+        const hipError_t e = hipFuncSetAttribute((const void*)k_timecorr_mfma<kOdd, kWide>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds(kMaxLtTime));
         if (e != hipSuccess) return e;
         lds_set = true;
     }
-    const int grid = std::min(ncfg, 2 * ncu);
-    hipLaunchKernelGGL(k_timecorr_mfma<RR>, dim3(grid), dim3(64 * kTcWaves), lds, st, sh, cfg0, ncfg, rec);
+    // Up to four workgroups share a configuration's tiles and add up, 32 or
+    // more tiles to a wave (Ltau = 2048: 1647 -> 1508 us with four: fewer
+    // configurations at a time through an L2, and the dispatcher evens out
+    // the workgroups); more where there are few configurations.
+    const int ntt = (sh.Lt + 63) / 64, ntp = ntt * (ntt + 1) / 2;
+    int nsplit = std::max(1, std::min(4, ntp / (32 * kTcWaves)));
+    while (ncfg * nsplit < 2 * ncu && kTcWaves * nsplit < ntp) nsplit *= 2;
+    const bool grouped = ncu % 8 == 0 && ncfg >= 128;
+    if (nsplit > 1) {
+        const size_t n = (size_t)ncfg * 2 * sh.Lt;
+        hipLaunchKernelGGL(k_zero_time, dim3((unsigned)std::min<size_t>((n + 255) / 256, 1024)), dim3(256), 0, st, rec,
+                           n);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_timecorr_mfma<kOdd, kWide>), dim3((unsigned)((grouped ? (ncfg + 7) / 8 * 8 : ncfg) * nsplit)),
+                       dim3(64 * kTcWaves), lds(sh.Lt), st, sh, cfg0, ncfg, nsplit, (int)grouped, rec);
     return hipGetLastError();
 }
 
@@ -258,15 +257,12 @@ size_t timecorr_record_bytes(const ShapeDev& sh, int ncfg) { return (size_t)ncfg
 
 hipError_t launch_timecorr(const ShapeDev& sh, int cfg0, int ncfg, int64_t* rec, hipStream_t st) {
     if (ncfg <= 0) return hipSuccess;
-    switch (sh.R) {
-        case 1: return launch_timecorr_rr<1>(sh, cfg0, ncfg, rec, st);
-        case 2: return launch_timecorr_rr<2>(sh, cfg0, ncfg, rec, st);
-        case 3: return launch_timecorr_rr<3>(sh, cfg0, ncfg, rec, st);
-        case 4: return launch_timecorr_rr<4>(sh, cfg0, ncfg, rec, st);
-        case 5: return launch_timecorr_rr<5>(sh, cfg0, ncfg, rec, st);
-        case 6: return launch_timecorr_rr<6>(sh, cfg0, ncfg, rec, st);
-        default: return hipErrorInvalidValue;
-    }
+    const bool wide = (unsigned long long)sh.R * sh.L2 * sh.L2 * sh.Lt >= 1ull << 32;
+    if (sh.nx & 1)
+        return wide ? launch_timecorr_as<true, true>(sh, cfg0, ncfg, rec, st)
+                    : launch_timecorr_as<true, false>(sh, cfg0, ncfg, rec, st);
+    return wide ? launch_timecorr_as<false, true>(sh, cfg0, ncfg, rec, st)
+                : launch_timecorr_as<false, false>(sh, cfg0, ncfg, rec, st);
 }
 
 }  // namespace tfim
