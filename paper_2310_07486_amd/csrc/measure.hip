@@ -35,6 +35,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "gram_tile.h"
 #include "tfim_internal.h"
 
 namespace tfim {
@@ -133,11 +134,9 @@ __global__ void __launch_bounds__(256) k_transpose(ShapeDev sh, long long items)
 // ---------------------------------------------------------------------------
 // G tiles and the D buckets (Ltau <= 8192).
 //
-// Sites stand in blocks of 32 rows: block (a, b) holds x1 = 4a .. 4a + 3 and
-// x2 = 8b .. 8b + 7 (row 4 (x2 - 8b) + x1 - 4a), so that the 16 elements q of
-// a lane in the 32 x 32 MFMA layout take four values of x1 - y1 (by q mod 4)
-// and four of x2 - y2 (by q div 4), for every even L.  Blocks are taken two
-// at a time: a tile is 2 x 2 blocks, tiles X <= Y of the upper triangle.
+// Tiles X <= Y of the upper triangle, 2 x 2 blocks of 4 x 8 sites each, in
+// which the 16 elements q of a lane take four values of x1 - y1 (by q mod 4)
+// and four of x2 - y2 (by q div 4).
 //
 // Each wave works alone on one tile (no barrier inside it), the replicas in
 // turn: the K loop of one replica runs on 64 fp32 accumulators (fp4 operands
@@ -183,7 +182,6 @@ constexpr unsigned long long kSqBias = 0x4B000000ull;  // the bits of 2^23
 constexpr int kNarrowLt = 8192;  // |G| <= 2^13: int16 digits, int32 lane sums
 __host__ __device__ constexpr int gram_pitch(int P) { return P | 1; }  // pairs, padded to an odd count
 
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef short i16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int mad_lo16(int a, int b, int c) {
     int d;
@@ -205,10 +203,10 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg, int ncw, int nsplit, int ncopy, int
     constexpr int PP = RR * (RR - 1) / 2, PT = gram_pitch(PP);
     extern __shared__ __align__(16) uint8_t smem[];
     unsigned long long* const Bk = (unsigned long long*)smem;  // [ncw][F, U][x, y][L][ncopy][PT]
-    const int L = sh.L, Lt = sh.Lt, nc = sh.nc, nxp = sh.nxp;
+    const int L = sh.L;
     const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nb8 = (L + 7) >> 3, nblk = ((L + 3) >> 2) * nb8;
+    const int nb8 = gram_nb8(L), nblk = gram_nblk(L);
     const int ntile = (nblk + 1) >> 1, ntp = ntile * (ntile + 1) / 2;
     // grouped: workgroup b runs on XCD b mod 8, which takes the configurations
     // b mod 8, b mod 8 + 8, ... (times ncw), so that the nsplit workgroups of one
@@ -220,96 +218,29 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg, int ncw, int nsplit, int ncopy, int
     const int half = 2 * L * ncopy * PT;  // words of F or of U of one configuration
     for (int e = tid; e < ncl * 2 * half; e += 64 * kGramWaves) Bk[e] = 0;
     __syncthreads();
-    // Lane (i, h) takes the whole word of chunk 2c + h, whose halves feed two
-    // MFMAs: one 8-byte load per row and 128 values of tau, 256 consecutive
-    // bytes per half-wave.  In the last pair: the last chunk's bits past Ltau
-    // (half of them turned over; their number is a multiple of 8), and with an
-    // odd number of chunks the half-wave h = 1 counts for nothing.
-    const int padn = (64 * nc - Lt) >> 1;
-    const uint64_t flip64 = padn && h == ((nc - 1) & 1) ? ~0ull << (64 - padn) : 0ull;
-    const uint32_t flip[2] = {(uint32_t)flip64, (uint32_t)(flip64 >> 32)};
-    const bool beyond = (nc & 1) && h == 1;
-    const uint32_t in_last = beyond ? 0u : ~0u;
-    const int back_last = beyond ? 8 * nxp : 0;  // such lanes read the last chunk instead
+    GramTile tile(sh);
     f32x16 start;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) start[q] = 12582912.0f;
+    for (int q = 0; q < 16; ++q) start[q] = kGramStart;
     for (int unit = part * kGramWaves + wv; unit < ncl * ntp; unit += kGramWaves * nsplit) {
         const int cl = unit / ntp;
         int X = 0, rem = unit - cl * ntp;
         while (rem >= ntile - X) { rem -= ntile - X; ++X; }
         const int Y = X + rem;
-        const uint64_t* const pt = sh.Pt + (size_t)(cfg0 + c0 + cl) * RR * nc * nxp;
-        const uint32_t base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)pt);
-        const uint32_t base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)pt >> 32));
-        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(((uint64_t)base_hi << 32) | base_lo), (short)0, RR * nc * nxp * 8, 0x00020000);
-        int voff[4];         // byte offset of this lane's row (chunk h of a pair) in the row blocks, then the columns
-        uint32_t mag[4];     // 0 on a padding site
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int blk = 2 * (k < 2 ? X : Y) + (k & 1);
-            const int x1 = 4 * (blk / nb8) + (i & 3), x2 = 8 * (blk % nb8) + (i >> 2);
-            const bool ok = blk < nblk && x1 < L && x2 < L;
-            voff[k] = 8 * ((ok ? site_slot(L, x1, x2) : 0) + h * nxp);
-            mag[k] = ok ? 0x22222222u : 0u;
-        }
+        tile.configuration(sh, cfg0 + c0 + cl);
+        tile.tile(L, X, Y);
         int pk[RR][2][2][8];  // G of elements 2t, 2t + 1
 #pragma unroll
         for (int r = 0; r < RR; ++r) {
             f32x16 acc[2][2];
-            auto fetch = [&](int c, u32x2 (&w)[4]) {
-                const int so = (r * nc + 2 * c) * nxp * 8;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) w[k] = __builtin_amdgcn_raw_buffer_load_b64(rows, voff[k], so, 0);
-            };
-            auto chunk = [&](const u32x2 (&w)[4], auto firstC) {
-                constexpr bool kFirst = decltype(firstC)::value;
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    i32x4 o[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        o[k] = fp4_signs_operand(kFirst && k < 2 ? w[k][ks] ^ flip[ks] : w[k][ks],
-                                                 kFirst && k < 2 ? mag[k] & in_last : mag[k]);
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int v = 0; v < 2; ++v)
-                            acc[u][v] = mfma_fp4(fp4_wide(o[u]), fp4_wide(o[2 + v]),
-                                                 kFirst && ks == 0 ? start : acc[u][v]);
-                }
-            };
-            // the last pair of chunks first (it starts the accumulators), then
-            // pairs 0 .. n - 1, two word sets in turn, each loaded two pairs
-            // ahead (past the end: the last one again, not used)
-            const int n = (nc + 1) / 2 - 1;
-            u32x2 w0[4], w1[4];
-            {
-                const int so = (r * nc + 2 * n) * nxp * 8;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    w1[k] = __builtin_amdgcn_raw_buffer_load_b64(rows, voff[k] - back_last, so, 0);
-            }
-            fetch(0, w0);
-            chunk(w1, std::true_type{});
-            fetch(min(1, n), w1);
-            int c = 0;
-            for (; c + 1 < n; c += 2) {
-                chunk(w0, std::false_type{});
-                fetch(min(c + 2, n), w0);
-                chunk(w1, std::false_type{});
-                fetch(min(c + 3, n), w1);
-            }
-            if (c < n) chunk(w0, std::false_type{});
+            tile.product(r, start, acc);
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
                 for (int v = 0; v < 2; ++v)
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
-                        pk[r][u][v][t] = (int)__builtin_amdgcn_perm(__float_as_uint(acc[u][v][2 * t + 1]),
-                                                                    __float_as_uint(acc[u][v][2 * t]), 0x05040100u);
+                        pk[r][u][v][t] = gram_pack(acc[u][v], t);
                         asm volatile("" : "+v"(pk[r][u][v][t]));  // packed here, not where it is used
                     }
             __builtin_amdgcn_sched_barrier(0);  // the next replica's loads wait until the accumulators are free
@@ -321,12 +252,11 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg, int ncw, int nsplit, int ncopy, int
                 if (X == Y && u == 1 && v == 0) continue;
                 const int br = 2 * X + u, bc = 2 * Y + v;
                 unsigned long long* const B0 = Bk + cl * 2 * half + (X == Y && u == v ? 0 : half);
-                auto wrap = [L](int d) { return d < 0 ? d + L : (d >= L ? d - L : d); };
                 unsigned long long *bx[4], *by[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int dx = wrap(4 * (br / nb8 - bc / nb8) + j - (i & 3));
-                    const int dy = wrap(8 * (br % nb8 - bc % nb8) + 2 * j + h - (i >> 2));
+                    const int dx = bucket_of(4 * (br / nb8 - bc / nb8) + j - (i & 3), L);
+                    const int dy = bucket_of(8 * (br % nb8 - bc % nb8) + 2 * j + h - (i >> 2), L);
                     bx[j] = B0 + (dx * ncopy + ((i >> 2) & (ncopy - 1))) * PT;
                     by[j] = B0 + ((L + dy) * ncopy + (((i & 3) + 4 * h) & (ncopy - 1))) * PT;
                 }
@@ -962,7 +892,7 @@ hipError_t launch_gram(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStrea
     constexpr int PP = RR * (RR - 1) / 2;
     // tiles per configuration: four, two or one configuration at a time give
     // each of the four waves a tile (L <= 8: one tile, L <= 16: 6 or 10)
-    const int nblk = ((sh.L + 3) / 4) * ((sh.L + 7) / 8), ntile = (nblk + 1) / 2, ntp = ntile * (ntile + 1) / 2;
+    const int nblk = gram_nblk(sh.L), ntile = (nblk + 1) / 2, ntp = ntile * (ntile + 1) / 2;
     int ncw = ntp == 1 ? 4 : (ntp <= 10 ? 2 : 1);
     while (ncw > 1 && (ncfg + ncw - 1) / ncw < 2 * ncu) ncw /= 2;
     const int nitem = (ncfg + ncw - 1) / ncw;
