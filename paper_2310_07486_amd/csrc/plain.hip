@@ -67,12 +67,11 @@ __global__ void k_plain_init_spins(ShapeDev sh, uint32_t key0, uint32_t key1) {
 // R < Tu[k-index][u] with u = (12 - dE)/4 unsatisfied bonds.  Sites of one
 // colour only neighbour the other colour, so threads never race.
 __global__ void __launch_bounds__(256) k_plain_half(ShapeDev sh, uint32_t key0, uint32_t key1,
-                                                    const Counters* __restrict__ ctr, int c) {
+                                                    uint32_t t, int c) {
     int8_t* S8 = (int8_t*)sh.S;
     const int8_t* J = (const int8_t*)sh.J;
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W;
     const int nq = (Lt + 7) / 8;
-    const uint32_t t = ctr->t;
     const int sgn = sh.apm ? -1 : 1;
     const size_t total = (size_t)sh.R * nk * ns * L2 * nq;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
@@ -148,9 +147,8 @@ __global__ void __launch_bounds__(256) k_plain_energy(ShapeDev sh) {
 // ...; d = U_a - U_b of the walkers at k_i, k_{i+1}; accept iff d <= 0 or
 // R < Tpt[i][d] (the exchange ratio with E = 2U - 3N); R = output s%4 of the
 // Philox call ((s%64)/4 | i << 4, m, r, word j), one uniform per sample.
-__global__ void k_plain_temper(ShapeDev sh, uint32_t key0, uint32_t key1, const Counters* __restrict__ ctr) {
+__global__ void k_plain_temper(ShapeDev sh, uint32_t key0, uint32_t key1, uint32_t m) {
     const int nk = sh.nk, ns = sh.W;
-    const uint32_t m = ctr->m;
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= sh.R * ns) return;
     const int r = g / ns, s = g % ns;
@@ -315,21 +313,21 @@ hipError_t plain_energy(const ShapeDev& sh, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t plain_sweep(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st) {
+hipError_t plain_sweep(const ShapeDev& sh, uint64_t seed, uint32_t t, hipStream_t st) {
     const size_t total = (size_t)sh.R * sh.nk * sh.W * sh.L2 * ((sh.Lt + 7) / 8);
     for (int c = 0; c < 2; ++c) {
         hipLaunchKernelGGL(k_plain_half, dim3(grid_of(total)), dim3(256), 0, st, sh, (uint32_t)seed,
-                           (uint32_t)(seed >> 32), ctr, c);
+                           (uint32_t)(seed >> 32), t, c);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return plain_energy(sh, st);
 }
 
-hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st) {
+hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st) {
     const int n = sh.R * sh.W;
     hipLaunchKernelGGL(k_plain_temper, dim3((n + 63) / 64), dim3(64), 0, st, sh, (uint32_t)seed,
-                       (uint32_t)(seed >> 32), ctr);
+                       (uint32_t)(seed >> 32), m);
     return hipGetLastError();
 }
 

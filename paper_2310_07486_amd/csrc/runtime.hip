@@ -61,6 +61,7 @@ struct tfim_plan {
     // failure injection (TFIM_FAIL_AFTER): the n-th enqueueing call fails
     int64_t fail_after = 0;
     std::vector<uint64_t> t, m;  // host mirrors per shape
+    bool counters_behind = false;  // the device's counters are older than the mirrors
     uint32_t schedule = TFIM_SCHED_PER_SHAPE;
     int variant = 3;  // helper waves where L = 24, else the streaming kernel
     uint32_t measure_mode = 0;
@@ -584,21 +585,22 @@ static hipError_t timed_sweep(tfim_plan* pl, int i, bool energy) {
     std::pair<hipEvent_t, hipEvent_t> ev;
     hipError_t e = timing_begin(pl, ev);
     if (e == hipSuccess && plain(pl))
-        e = tfim::plain_sweep(dev_of(pl, i), pl->seed, counters_of(pl, i), pl->stream);
+        e = tfim::plain_sweep(dev_of(pl, i), pl->seed, (uint32_t)pl->t[i], pl->stream);
     else if (e == hipSuccess)
-        e = tfim::launch_sweep(dev_of(pl, i), pl->seed, counters_of(pl, i), pl->variant, energy,
-                               pl->stream);
+        e = tfim::launch_sweep(dev_of(pl, i), pl->seed, tfim::When{(uint32_t)pl->t[i], nullptr}, pl->variant, energy,
+                               pl->n_cu, pl->stream);
     return timing_end(pl, ev, 1, e);
 }
 
 static hipError_t temper(tfim_plan* pl, int i) {
-    if (plain(pl)) return tfim::plain_temper(dev_of(pl, i), pl->seed, counters_of(pl, i), pl->stream);
-    return tfim::launch_temper(dev_of(pl, i), pl->seed, counters_of(pl, i), pl->stream);
+    if (plain(pl)) return tfim::plain_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i], pl->stream);
+    return tfim::launch_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i], pl->stream);
 }
 
 // Enqueue one sweep of every shape (plus due tempering) with the per-shape
-// schedule; the host mirrors pl->t hold each shape's sweep counter.  U is
-// recounted when a tempering step follows or when the caller will see it.
+// schedule; the host mirrors pl->t, pl->m hold each shape's counters and go to
+// the kernels by value (the device's own counters serve the graphs of the other
+// schedules and are brought up to date before those).  U is recounted when a tempering step follows or when the caller will see it.
 static hipError_t enqueue_sweep(tfim_plan* pl, bool last) {
     hipError_t e = hipSuccess;
     const int ns = (int)pl->shapes.size();
@@ -611,8 +613,8 @@ static hipError_t enqueue_sweep(tfim_plan* pl, bool last) {
         const uint32_t pe = pl->shapes[i].s.pt_every;
         const bool due = pe > 0 && ((pl->t[i] + 1) % pe) == 0;
         if (due) e = temper(pl, i);
-        if (e == hipSuccess) e = tfim::launch_advance(counters_of(pl, i), 1u, due ? 1u : 0u, pl->stream);
     }
+    pl->counters_behind = true;
     return e;
 }
 
@@ -691,7 +693,7 @@ static tfim_status concurrent_setup(tfim_plan* pl) {
         e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
         if (e == hipSuccess) pl->ev_join.push_back(ev);
     }
-    for (int i = 0; i < ns && e == hipSuccess; ++i) e = tfim::prepare_sweep(dev_of(pl, i), pl->variant, true);
+    for (int i = 0; i < ns && e == hipSuccess; ++i) e = tfim::prepare_sweep(dev_of(pl, i), pl->variant, true, pl->n_cu);
     if (e != hipSuccess) return check_hip(pl, e, "concurrent setup");
     return pl->tables_up ? TFIM_OK : upload_tables(pl);
 }
@@ -793,8 +795,8 @@ static hipError_t batch_graph(tfim_plan* pl, uint32_t g, hipGraphExec_t* out) {
             for (int i = 0; i < ns && le == hipSuccess; ++i) {
                 le = hipStreamWaitEvent(pl->side[i], pl->ev_fork, 0);
                 if (le == hipSuccess)
-                    le = tfim::launch_sweep(dev_of(pl, i), pl->seed, counters_of(pl, i), pl->variant, true,
-                                            pl->side[i]);
+                    le = tfim::launch_sweep(dev_of(pl, i), pl->seed, tfim::When{0, counters_of(pl, i)}, pl->variant,
+                                            true, pl->n_cu, pl->side[i]);
                 if (le == hipSuccess) le = hipEventRecord(pl->ev_join[i], pl->side[i]);
                 if (le == hipSuccess) le = hipStreamWaitEvent(pl->cap_stream, pl->ev_join[i], 0);
             }
@@ -823,6 +825,16 @@ static hipError_t batch_graph(tfim_plan* pl, uint32_t g, hipGraphExec_t* out) {
 
 static hipError_t enqueue_batched(tfim_plan* pl, uint64_t n) {
     hipError_t e = hipSuccess;
+    if (pl->counters_behind) {
+        tfim::CounterValues v{};
+        for (size_t i = 0; i < pl->shapes.size(); ++i) {
+            v.t[i] = (uint32_t)pl->t[i];
+            v.m[i] = (uint32_t)pl->m[i];
+        }
+        e = tfim::launch_set_counters(counters_of(pl, 0), v, (int)pl->shapes.size(), pl->stream);
+        if (e != hipSuccess) return e;
+        pl->counters_behind = false;
+    }
     while (n > 0 && e == hipSuccess) {
         const uint32_t g = (uint32_t)std::min<uint64_t>(n, kGraphSweeps);
         hipGraphExec_t ex = nullptr;
@@ -879,9 +891,9 @@ tfim_status tfim_pt_swap(tfim_plan* pl) {
     hipError_t e = hipSuccess;
     for (size_t i = 0; i < pl->shapes.size() && e == hipSuccess; ++i) {
         e = temper(pl, (int)i);
-        if (e == hipSuccess) e = tfim::launch_advance(counters_of(pl, (int)i), 0u, 1u, pl->stream);
         pl->m[i] += 1;
     }
+    pl->counters_behind = true;
     return check_hip(pl, e, "pt_swap");
 }
 

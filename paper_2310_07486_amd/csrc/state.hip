@@ -128,9 +128,9 @@ __device__ void temper_group(const ShapeDev& sh, int r, int j, uint32_t key0, ui
 }
 
 __global__ void __launch_bounds__(kTemperThreads) k_temper(ShapeDev sh, uint32_t key0, uint32_t key1,
-                                               const Counters* __restrict__ ctr) {
+                                               uint32_t m) {
     extern __shared__ uint8_t kl[];  // [64][nk] labels, then [64][nk] inverse
-    temper_group(sh, (int)blockIdx.x / sh.W, (int)blockIdx.x % sh.W, key0, key1, ctr->m, kl);
+    temper_group(sh, (int)blockIdx.x / sh.W, (int)blockIdx.x % sh.W, key0, key1, m, kl);
 }
 
 __device__ __forceinline__ bool pt_due(const ShapeDev& sh, uint32_t t) {
@@ -160,10 +160,11 @@ __global__ void k_advance_batch(TemperBatchArgs a) {
     }
 }
 
-__global__ void k_advance(Counters* ctr, uint32_t dt, uint32_t dm) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        ctr->t += dt;
-        ctr->m += dm;
+__global__ void k_set_counters(Counters* ctr, CounterValues v, int n) {
+    const int s = threadIdx.x;
+    if (s < n) {
+        ctr[s].t = v.t[s];
+        ctr[s].m = v.m[s];
     }
 }
 
@@ -201,9 +202,9 @@ hipError_t launch_mask_rebuild(const ShapeDev& sh, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st) {
+hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st) {
     hipLaunchKernelGGL(k_temper, dim3(sh.R * sh.W), dim3(kTemperThreads), (size_t)128 * sh.nk, st, sh,
-                       (uint32_t)seed, (uint32_t)(seed >> 32), ctr);
+                       (uint32_t)seed, (uint32_t)(seed >> 32), m);
     return hipGetLastError();
 }
 
@@ -217,8 +218,8 @@ hipError_t launch_advance_batch(const TemperBatchArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_advance(Counters* ctr, uint32_t dt, uint32_t dm, hipStream_t st) {
-    hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, st, ctr, dt, dm);
+hipError_t launch_set_counters(Counters* ctr, const CounterValues& v, int n, hipStream_t st) {
+    hipLaunchKernelGGL(k_set_counters, dim3(1), dim3(64), 0, st, ctr, v, n);
     return hipGetLastError();
 }
 

@@ -180,8 +180,7 @@ __device__ inline void store_chunk(const Chunk& c, uint64_t* col, int q, int p, 
     }
 }
 
-__global__ void __launch_bounds__(kMaxThreads) k_sweep_fused(ShapeDev sh, uint32_t key0, uint32_t key1,
-                                                      const Counters* __restrict__ ctr) {
+__global__ void __launch_bounds__(kMaxThreads) k_sweep_fused(ShapeDev sh, uint32_t key0, uint32_t key1, When when) {
     extern __shared__ uint64_t lds[];
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, W = sh.W;
     const int H = L2 >> 1;  // half-plane words
@@ -204,7 +203,7 @@ __global__ void __launch_bounds__(kMaxThreads) k_sweep_fused(ShapeDev sh, uint32
     for (int i = tid; i < 3 * nk; i += blockDim.x) Tu_lds[i] = sh.Tu[i];
     if (tid < 64) Ublk[tid] = 0;
 
-    const uint32_t t = ctr->t;
+    const uint32_t t = when.get();
     const uint32_t c3 = ctr_word3(sh.word_offset + (uint32_t)j, sh.sid, kTagMetro);
     const uint32_t c2base = (uint32_t)rw << 1;
 
@@ -421,18 +420,26 @@ const char* sweep_variant_name(int v) {
     }
 }
 
-hipError_t launch_sweep(const ShapeDev& sh, uint64_t seed, const Counters* ctr, int variant,
-                        bool energy, hipStream_t st) {
-    if (variant == 3 && sweep_helped_ok(sh)) return launch_sweep_helped(sh, seed, ctr, energy, st);
+hipError_t launch_sweep(const ShapeDev& sh, uint64_t seed, When t, int variant, bool energy, int ncu,
+                        hipStream_t st) {
+    if ((variant == 0 || variant == 3) && sweep_stream_ok(sh)) {
+        const int nparts = sweep_parts(sh, energy, ncu);
+        if (nparts > 1) return launch_sweep_parts(sh, seed, t, energy, nparts, st);
+    }
+    if (variant == 3 && sweep_helped_ok(sh)) return launch_sweep_helped(sh, seed, t, energy, st);
     if ((variant == 0 || variant == 2 || variant == 3) && sweep_stream_ok(sh))
-        return launch_sweep_stream(sh, seed, ctr, energy, variant == 2 ? 5 : 1, st);
+        return launch_sweep_stream(sh, seed, t, energy, variant == 2 ? 5 : 1, st);
     const int nblk = sh.R * sh.nk * sh.W;
     hipLaunchKernelGGL(k_sweep_fused, dim3(nblk), dim3(block_for(sh)), sweep_lds_bytes(sh), st, sh,
-                       (uint32_t)seed, (uint32_t)(seed >> 32), ctr);
+                       (uint32_t)seed, (uint32_t)(seed >> 32), t);
     return hipGetLastError();
 }
 
-hipError_t prepare_sweep(const ShapeDev& sh, int variant, bool energy) {
+hipError_t prepare_sweep(const ShapeDev& sh, int variant, bool energy, int ncu) {
+    if ((variant == 0 || variant == 3) && sweep_stream_ok(sh)) {
+        const int nparts = sweep_parts(sh, energy, ncu);
+        if (nparts > 1) return launch_sweep_parts(sh, 0, When{0, nullptr}, energy, nparts, nullptr, false);
+    }
     if (variant == 3 && sweep_helped_ok(sh)) return prepare_sweep_helped(sh, energy);
     if ((variant == 0 || variant == 2 || variant == 3) && sweep_stream_ok(sh))
         return prepare_sweep_stream(sh, energy, variant == 2 ? 5 : 1);

@@ -31,6 +31,7 @@
 // The colour-1 update also yields, per lane, the number of unsatisfied bonds
 // of its site in the final state; summing it over the colour-1 sites gives U
 // exactly (every bond joins a colour-0 and a colour-1 site).
+#include <algorithm>
 #include <type_traits>
 
 #include "tfim_internal.h"
@@ -284,12 +285,16 @@ __host__ __device__ inline int stream_cols(const ShapeDev& sh) { return ((sh.L2 
 // kPacked = false: one team filling the workgroup (g = nlive = 1,
 // cols = blockDim.x), so every wave is a live member.  kDeepLds: the energy
 // counters live in LDS rather than registers.
-template <bool kE, bool kPacked, bool kDeepLds, bool kAnti>
+// kPart: only the planes t0 .. t0 + M - 1 (multiples of 8) of the configuration
+// (k_sweep_part); else t0 = 0, M = Ltau.
+template <bool kE, bool kPacked, bool kDeepLds, bool kAnti, bool kPart = false>
 __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, const int g,
                                             const int nlive, const int cols, uint64_t* lds,
                                             const uint32_t key0, const uint32_t key1,
-                                            const uint32_t t) {
+                                            const uint32_t t, const int t0_ = 0, const int M_ = 0,
+                                            uint32_t* const Upart = nullptr) {
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, W = sh.W;
+    const int t0 = kPart ? t0_ : 0, M = kPart ? M_ : Lt;
     const int nb0 = sh.bnb[0] + 1, nb1 = sh.bnb[1] + 1, nb2 = sh.bnb[2] + 1;
     const int nbt = nb0 + nb1 + nb2;
     const int tid = threadIdx.x, nthr = blockDim.x;
@@ -314,33 +319,6 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
     const int rw = cfg / W;
     const int w = rw % nk;
     const int r = rw / nk;
-
-    if (member)
-        for (int i = ttid; i <= nk; i += cols)
-            ml[i] = live ? sh.mask[((size_t)(r * W + j) * nk + w) * (nk + 1) + i] : 0ull;
-    if (kE && member && ttid < 64) Ublk[ttid] = 0;
-    if (kE && kDeepLds)
-        for (int i = 0; i < kDeep; ++i) DEEP[i * nthr + tid] = 0;
-    __syncthreads();
-    // entry a of the concatenated tables (u = 0, 1, 2) sits at btab[a + shift(u)]
-    const int bo0 = sh.boff[0], bo1 = sh.boff[1] - nb0, bo2 = sh.boff[2] - nb0 - nb1;
-    for (int a = tid; a < nbt; a += nthr)
-        TT[a] = (uint32_t)sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
-    if (member)
-        for (int a = ttid; a < nbt; a += cols) {
-            const uint64_t e = sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
-            const uint32_t kb = (uint32_t)(e >> 32) & 0xFFFFu, mu = (uint32_t)(e >> 48);
-            MM[2 * a] = ml[kb];
-            MM[2 * a + 1] = ml[kb + mu];
-        }
-    Tables tb;
-    tb.T[0] = TT; tb.T[1] = TT + nb0; tb.T[2] = TT + nb0 + nb1;
-    tb.M[0] = MM; tb.M[1] = MM + 2 * nb0; tb.M[2] = MM + 2 * (nb0 + nb1);
-    tb.sh[0] = (uint32_t)sh.bsh[0]; tb.sh[1] = (uint32_t)sh.bsh[1]; tb.sh[2] = (uint32_t)sh.bsh[2];
-    tb.nb[0] = (uint32_t)sh.bnb[0]; tb.nb[1] = (uint32_t)sh.bnb[1]; tb.nb[2] = (uint32_t)sh.bnb[2];
-
-    const uint32_t c3 = ctr_word3(sh.word_offset + (uint32_t)j, sh.sid, kTagMetro);
-    const uint32_t c2_0 = (uint32_t)rw << 1, c2_1 = c2_0 | 1u;
 
     const int xy = active ? ttid : 0;
     const int x = xy % L, y = xy / L;
@@ -368,19 +346,27 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
         (void*)(((uint64_t)base_hi << 32) | base_lo), (short)0, nbytes, kBufferWord3);
     const int voff = 8 * xy;
     const int plane = 8 * L2;      // bytes per tau plane
-    const int half = Lt >> 1;      // colour-0 steps
-    const int nq = Lt >> 3;        // Philox groups per colour and column
-    auto wrap = [Lt](int P) { return P >= Lt ? P - Lt : (P < 0 ? P + Lt : P); };
+    const int half = M >> 1;       // colour-0 steps
+    const int nq = M >> 3;         // Philox groups per colour and column
+    const int q0 = t0 >> 3;        // the first of them
+    // planes are counted from t0
+    auto wrap = [Lt, t0](int P) {
+        if constexpr (kPart) P += t0;
+        return P >= Lt ? P - Lt : (P < 0 ? P + Lt : P);
+    };
     // a plane reached across the tau wrap (P < 0 or P >= Ltau) is read
     // complemented and stored back complemented when the boundary is
     // antiperiodic: the wrap bond then has the sign -1 (apm = all ones).
     // kAnti = false compiles the periodic kernel without any of it.
     const uint64_t apm = kAnti ? sh.apm : 0ull;
-    auto across = [Lt, apm](int P) -> uint64_t { return (kAnti && (P < 0 || P >= Lt)) ? apm : 0ull; };
-    // uniform plane P; planes past Lt + 1 are never used: the load is
+    auto across = [Lt, apm, t0](int P) -> uint64_t {
+        if constexpr (kPart) P += t0;
+        return (kAnti && (P < 0 || P >= Lt)) ? apm : 0ull;
+    };
+    // uniform plane P; planes past M + 1 are never used: the load is
     // clamped, not skipped
     auto ld = [&](int P) -> uint64_t {
-        const int Q = min(P, Lt + 1);
+        const int Q = min(P, M + 1);
         return buf_load(spins, voff, wrap(Q) * plane) ^ across(Q);
     };
     // per-lane plane P (prologue): the plane offset goes in the vector offset
@@ -391,12 +377,39 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
     w3 = ld_lane(p - 1);
     w4 = ld_lane(p);
     w5 = ld_lane(p + 1);
-    pf0 = ld_lane(min(p + 2, Lt + 1));
-    pf1 = ld_lane(min(p + 3, Lt + 1));
+    pf0 = ld_lane(min(p + 2, M + 1));
+    pf1 = ld_lane(min(p + 3, M + 1));
     uint64_t pu1 = ld(4);  // plane 2 sigma + 4 of the next segment for parity 0
     // steady state: planes A + 4, A + 5 of the next segment, already in flight
     const int voffp = voff + p * plane;
     uint64_t nn0 = ld_lane(p + 4), nn1 = ld_lane(p + 5);
+    if (member)
+        for (int i = ttid; i <= nk; i += cols)
+            ml[i] = live ? sh.mask[((size_t)(r * W + j) * nk + w) * (nk + 1) + i] : 0ull;
+    if (kE && member && ttid < 64) Ublk[ttid] = 0;
+    if (kE && kDeepLds)
+        for (int i = 0; i < kDeep; ++i) DEEP[i * nthr + tid] = 0;
+    __syncthreads();
+    // entry a of the concatenated tables (u = 0, 1, 2) sits at btab[a + shift(u)]
+    const int bo0 = sh.boff[0], bo1 = sh.boff[1] - nb0, bo2 = sh.boff[2] - nb0 - nb1;
+    for (int a = tid; a < nbt; a += nthr)
+        TT[a] = (uint32_t)sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
+    if (member)
+        for (int a = ttid; a < nbt; a += cols) {
+            const uint64_t e = sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
+            const uint32_t kb = (uint32_t)(e >> 32) & 0xFFFFu, mu = (uint32_t)(e >> 48);
+            MM[2 * a] = ml[kb];
+            MM[2 * a + 1] = ml[kb + mu];
+        }
+    Tables tb;
+    tb.T[0] = TT; tb.T[1] = TT + nb0; tb.T[2] = TT + nb0 + nb1;
+    tb.M[0] = MM; tb.M[1] = MM + 2 * nb0; tb.M[2] = MM + 2 * (nb0 + nb1);
+    tb.sh[0] = (uint32_t)sh.bsh[0]; tb.sh[1] = (uint32_t)sh.bsh[1]; tb.sh[2] = (uint32_t)sh.bsh[2];
+    tb.nb[0] = (uint32_t)sh.bnb[0]; tb.nb[1] = (uint32_t)sh.bnb[1]; tb.nb[2] = (uint32_t)sh.bnb[2];
+
+    const uint32_t c3 = ctr_word3(sh.word_offset + (uint32_t)j, sh.sid, kTagMetro);
+    const uint32_t c2_0 = (uint32_t)rw << 1, c2_1 = c2_0 | 1u;
+
     u32x4 G0 = 0, G1 = 0;
     uint32_t prevlast = 0;
     uint64_t sm[5] = {0, 0, 0, 0, 0};
@@ -444,8 +457,8 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
             // as A + 4, A + 5 (no select that would wait for them at once)
             nx0 = nn0;
             nx1 = nn1;
-            nn0 = buf_load(spins, voffp, (2 * sigma + 6) * plane);
-            nn1 = buf_load(spins, voffp, (2 * sigma + 7) * plane);
+            nn0 = buf_load(spins, voffp, (t0 + 2 * sigma + 6) * plane);
+            nn1 = buf_load(spins, voffp, (t0 + 2 * sigma + 7) * plane);
         } else {
             // every load instruction reads whole planes 2 sigma + 5 and
             // 2 sigma + 6 (all columns, full cache lines); a thread keeps the
@@ -456,7 +469,7 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
             pu1 = u1;
         }
         if (do_c0) {
-            if (IS == 0) G0 = philox_dev((uint32_t)(xy + L2 * (sigma >> 2)), t, c2_0, c3, key0, key1);
+            if (IS == 0) G0 = philox_dev((uint32_t)(xy + L2 * (q0 + (sigma >> 2))), t, c2_0, c3, key0, key1);
             const uint64_t* Xb = X + (IS & 1) * H;
             const Nb n{Xb[hxp], Xb[hxm], Xb[hyp], Xb[hym]};
             uint64_t d0, d1, d2;
@@ -466,7 +479,7 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
             prevlast = G1[3];
             int q = (sigma - 1) >> 2;
             if (q >= nq) q -= nq;
-            G1 = philox_dev((uint32_t)(xy + L2 * q), t, c2_1, c3, key0, key1);
+            G1 = philox_dev((uint32_t)(xy + L2 * (q0 + q)), t, c2_1, c3, key0, key1);
         }
         if (do_c1) {
             constexpr int S3 = (IS + 3) & 3;  // (sigma - 1) & 3
@@ -517,12 +530,20 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
     segment(sl + 3, I3{}, B0{}, true, true);
     if (kE) add_deep(deep, sm);  // the 5-bit counters hold at most four sites
     segment(half, I0{}, B0{}, false, true);      // colour 1, step half-1
-    segment(half + 1, I1{}, B0{}, false, true);  // colour 1, step half == step 0 (tau wrap)
+    if constexpr (kPart) {
+        // the last colour-1 step reaches into the next part: k_sweep_join.  Plane
+        // M - 1 holds the new colour 0 and the old colour 1.
+        if (lane_ok) buf_store(p ? w0 : w1, spins, voff, wrap(M - 1) * plane);
+    } else {
+        segment(half + 1, I1{}, B0{}, false, true);  // colour 1, step half == step 0 (tau wrap)
+    }
     if (kE) {
         add_deep(deep, sm);
         flush_deep(deep, Ublk, true);
         __syncthreads();
-        if (live && ttid < 64) sh.U[((size_t)r * W * 64 + (size_t)j * 64 + ttid) * nk + w] = Ublk[ttid];
+        if constexpr (kPart) {
+            if (ttid < 64) Upart[ttid] = Ublk[ttid];
+        } else if (live && ttid < 64) sh.U[((size_t)r * W * 64 + (size_t)j * 64 + ttid) * nk + w] = Ublk[ttid];
     }
 }
 
@@ -823,9 +844,9 @@ __device__ __forceinline__ void helped_body(const ShapeDev& sh, const int cfg, u
 
 template <bool kE, bool kAnti>
 __global__ void __launch_bounds__(kHelpedThreads)
-k_sweep_helped(ShapeDev sh, uint32_t key0, uint32_t key1, const Counters* __restrict__ ctr) {
+k_sweep_helped(ShapeDev sh, uint32_t key0, uint32_t key1, When when) {
     extern __shared__ uint64_t lds[];
-    helped_body<kE, kAnti>(sh, (int)blockIdx.x, lds, key0, key1, ctr->t);
+    helped_body<kE, kAnti>(sh, (int)blockIdx.x, lds, key0, key1, when.get());
 }
 
 // One configuration per workgroup (r, w, j) = blockIdx.x.
@@ -834,10 +855,101 @@ k_sweep_helped(ShapeDev sh, uint32_t key0, uint32_t key1, const Counters* __rest
 // energy counters move to LDS to fit the smaller register budget.
 template <bool kE, int kOcc, bool kAnti>
 __global__ void __launch_bounds__(kMaxCols) __attribute__((amdgpu_waves_per_eu(kOcc)))
-k_sweep_stream(ShapeDev sh, uint32_t key0, uint32_t key1, const Counters* __restrict__ ctr) {
+k_sweep_stream(ShapeDev sh, uint32_t key0, uint32_t key1, When when) {
     extern __shared__ uint64_t lds[];
     sweep_teams<kE, false, (kOcc > 1), kAnti>(sh, (int)blockIdx.x, 1, 1, (int)blockDim.x, lds, key0, key1,
-                                              ctr->t);
+                                              when.get());
+}
+
+// A sweep of few configurations in parts along tau, several workgroups to a
+// configuration, so that a short chain fills the chip (one workgroup walks
+// Ltau / 2 dependent segments of about 0.5 us).  k_sweep_part sweeps planes
+// t0 .. t0 + M - 1 of each part: colour 0 everywhere, colour 1 except where it
+// needs the new colour 0 of another part, which is one colour-1 site per
+// column and boundary (plane t1 - 1 at parity 0, t1 at parity 1: what the
+// segment after the last would update).  Parts do not race: they read of each
+// other only those colour-1 words, which no part changes (a part stores the
+// old value back).  k_sweep_join then updates them, every neighbour new, and
+// adds up U.  The same numbers, so the same bits as k_sweep_stream.
+// Measured, us per sweep, parts and join: L = 12, Ltau = 512, 144
+// configurations 147 -> 47 + 6 (8 parts); L = 16, Ltau = 256, 128 configurations,
+// U counted 94 -> 40 + 9 (6 parts); L = 4, Ltau = 256, two configurations 63 ->
+// 6 + 4 (32 parts); L = 24, Ltau = 2048, 128 configurations 865 -> 598 (2 parts).
+template <bool kE, bool kAnti>
+__global__ void __launch_bounds__(kMaxCols)
+k_sweep_part(ShapeDev sh, uint32_t key0, uint32_t key1, When when, int nparts, int M, uint32_t* Upart) {
+    extern __shared__ uint64_t lds[];
+    const int cfg = (int)blockIdx.x / nparts, part = (int)blockIdx.x - cfg * nparts;
+    sweep_teams<kE, false, false, kAnti, true>(sh, cfg, 1, 1, (int)blockDim.x, lds, key0, key1, when.get(), part * M,
+                                               min(M, sh.Lt - part * M), Upart + 64 * (size_t)blockIdx.x);
+}
+
+// One workgroup per configuration: the colour-1 sites at the boundaries of the
+// parts (all at once: they are no neighbours of each other).
+constexpr int kJoinThreads = 1024;
+template <bool kE>
+__global__ void __launch_bounds__(kJoinThreads)
+k_sweep_join(ShapeDev sh, uint32_t key0, uint32_t key1, When when, int nparts, int M, const uint32_t* Upart) {
+    const uint32_t t = when.get();
+    extern __shared__ uint64_t lds[];
+    const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, W = sh.W;
+    uint64_t* const ml = lds;                         // [nk + 1] lane masks
+    uint32_t* const Ublk = (uint32_t*)(ml + nk + 1);  // [64]
+    const int cfg = blockIdx.x, j = cfg % W, rw = cfg / W, w = rw % nk, r = rw / nk, tid = threadIdx.x;
+    const int nthr = blockDim.x;
+    for (int i = tid; i <= nk; i += nthr) ml[i] = sh.mask[((size_t)(r * W + j) * nk + w) * (nk + 1) + i];
+    if (kE && tid < 64) Ublk[tid] = 0;
+    __syncthreads();
+    if (kE)
+        for (int i = tid; i < 64 * nparts; i += nthr) atomicAdd(&Ublk[i & 63], Upart[64 * (size_t)cfg * nparts + i]);
+    const uint32_t c3 = ctr_word3(sh.word_offset + (uint32_t)j, sh.sid, kTagMetro);
+    uint64_t* const S = sh.S + (size_t)cfg * Lt * L2;
+    const uint64_t* const Jb = sh.J + (size_t)j * 2 * L2;
+    auto mask = [&](int u, uint32_t R) {
+        const uint64_t e = sh.btab[sh.boff[u] + min((int)(R >> sh.bsh[u]), sh.bnb[u])];
+        return ml[((e >> 32) & 0xFFFFu) + (R < (uint32_t)e ? (uint32_t)(e >> 48) : 0u)];
+    };
+    uint64_t sm[5] = {0, 0, 0, 0, 0};
+    uint32_t held = 0;  // sites in sm (at most 4), uniform
+    uint32_t acc = 0;   // this lane's sample's unsatisfied bonds, over the wave's sites
+    auto flush = [&]() {
+        const int bits = held == 1 ? 3 : (held == 2 ? 4 : 5);  // at most 6 per site
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            if (k < bits) {
+                acc += (uint32_t)__popcll(wave_transpose64(sm[k])) << k;
+                sm[k] = 0;
+            }
+        held = 0;
+    };
+    for (int e0 = 0; e0 < nparts * L2; e0 += nthr) {  // uniform trip count: the flush needs whole waves
+        const int e = e0 + tid;
+        if (e < nparts * L2) {
+            const int d = e / L2, xy = e - d * L2, x = xy % L, y = xy / L, p = (x + y) & 1;
+            const int T = min((d + 1) * M, Lt) - 1 + p;  // plane of the site; Lt is plane 0
+            const int tau = T == Lt ? 0 : T;
+            const int tm = tau == 0 ? Lt - 1 : tau - 1, tp = tau == Lt - 1 ? 0 : tau + 1;
+            uint64_t* const P = S + (size_t)tau * L2;
+            const int xm = (x ? x - 1 : L - 1) + L * y, ym = x + L * (y ? y - 1 : L - 1);
+            const Nb n{P[(x + 1 == L ? 0 : x + 1) + L * y], P[xm], P[x + L * (y + 1 == L ? 0 : y + 1)], P[ym]};
+            const uint64_t up = S[(size_t)tp * L2 + xy] ^ (tau == Lt - 1 ? sh.apm : 0ull);
+            const uint64_t dn = S[(size_t)tm * L2 + xy] ^ (tau == 0 ? sh.apm : 0ull);
+            const int h = tau >> 1;
+            const u32x4 G = philox_dev((uint32_t)(xy + L2 * (h >> 2)), t, ((uint32_t)rw << 1) | 1u, c3, key0, key1);
+            const uint32_t R = (h & 2) ? ((h & 1) ? G.w : G.z) : ((h & 1) ? G.y : G.x);
+            uint64_t f0, f1, f2;
+            P[xy] = site_m<kE>(P[xy], n, Jb[xy], Jb[xm], Jb[L2 + xy], Jb[L2 + ym], up, dn, mask(0, R), mask(1, R),
+                               mask(2, R), f0, f1, f2);
+            if (kE) add3v(sm, f0, f1, f2);
+        }
+        if (kE && ++held == 4) flush();
+    }
+    if (kE) {
+        if (held) flush();
+        atomicAdd(&Ublk[tid & 63], acc);
+        __syncthreads();
+        if (tid < 64) sh.U[((size_t)r * W * 64 + (size_t)j * 64 + tid) * nk + w] = Ublk[tid];
+    }
 }
 
 // Persistent sweep of every shape of a plan in one launch.  Work items
@@ -922,59 +1034,100 @@ hipError_t prepare_sweep_stream(const ShapeDev& sh, bool energy, int occ) {
 }
 
 template <bool kE, int kOcc, bool kAnti>
-static hipError_t launch_one(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st) {
+static hipError_t launch_one(const ShapeDev& sh, uint64_t seed, When t, hipStream_t st) {
     const int nblk = sh.R * sh.nk * sh.W;
     const int threads = stream_cols(sh);
     const size_t lds = sweep_stream_lds_bytes(sh, 1, threads, kOcc > 1);
     hipError_t e = prepare_one<kE, kOcc, kAnti>(sh);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_sweep_stream<kE, kOcc, kAnti>), dim3(nblk), dim3(threads), lds, st, sh,
-                       (uint32_t)seed, (uint32_t)(seed >> 32), ctr);
+                       (uint32_t)seed, (uint32_t)(seed >> 32), t);
     return hipGetLastError();
 }
 
 template <bool kE, int kOcc>
-static hipError_t launch_bc(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st) {
-    return sh.apm ? launch_one<kE, kOcc, true>(sh, seed, ctr, st) : launch_one<kE, kOcc, false>(sh, seed, ctr, st);
+static hipError_t launch_bc(const ShapeDev& sh, uint64_t seed, When t, hipStream_t st) {
+    return sh.apm ? launch_one<kE, kOcc, true>(sh, seed, t, st) : launch_one<kE, kOcc, false>(sh, seed, t, st);
+}
+
+// Parts of a configuration that fill the chip: as many workgroups as are
+// resident at once (per CU 12 waves of the kernel that counts U, 16 of the
+// other); 1 where the configurations alone take more than half of them.
+int sweep_parts(const ShapeDev& sh, bool energy, int ncu) {
+    const int slots = ncu * std::max(1, (energy ? 12 : 16) / (stream_cols(sh) / 64)), ncfg = sh.R * sh.nk * sh.W, nq = sh.Lt >> 3;
+    const int want = std::min(nq, slots / ncfg);
+    if (want < 2) return 1;
+    const int per = (nq + want - 1) / want;  // groups of 8 planes per part
+    return (nq + per - 1) / per;
+}
+
+template <bool kE, bool kAnti>
+static hipError_t launch_parts_one(const ShapeDev& sh, uint64_t seed, When t, int nparts, hipStream_t st,
+                                   bool launch) {
+    static size_t lds_set = 0;
+    const int threads = stream_cols(sh), nq = sh.Lt >> 3, M = 8 * ((nq + nparts - 1) / nparts);
+    const int ncfg = sh.R * sh.nk * sh.W;
+    const size_t lds = sweep_stream_lds_bytes(sh, 1, threads, false);
+    hipError_t e = allow_lds((const void*)k_sweep_part<kE, kAnti>, lds, lds_set);
+    if (e != hipSuccess || !launch) return e;
+    // the parts' counts go where the bit layouts of the measurement lie: a
+    // sweep makes those out of date
+    uint32_t* const Upart = (uint32_t*)sh.Pt;
+    hipLaunchKernelGGL((k_sweep_part<kE, kAnti>), dim3(ncfg * nparts), dim3(threads), lds, st, sh, (uint32_t)seed,
+                       (uint32_t)(seed >> 32), t, nparts, M, Upart);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_sweep_join<kE>, dim3(ncfg),
+                       dim3(std::min(kJoinThreads, (nparts * sh.L2 + 63) / 64 * 64)), (size_t)(sh.nk + 1) * 8 + 256, st, sh, (uint32_t)seed,
+                       (uint32_t)(seed >> 32), t, nparts, M, (const uint32_t*)Upart);
+    return hipGetLastError();
+}
+
+hipError_t launch_sweep_parts(const ShapeDev& sh, uint64_t seed, When t, bool energy, int nparts, hipStream_t st,
+                              bool launch) {
+    if (energy)
+        return sh.apm ? launch_parts_one<true, true>(sh, seed, t, nparts, st, launch)
+                      : launch_parts_one<true, false>(sh, seed, t, nparts, st, launch);
+    return sh.apm ? launch_parts_one<false, true>(sh, seed, t, nparts, st, launch)
+                  : launch_parts_one<false, false>(sh, seed, t, nparts, st, launch);
 }
 
 bool sweep_helped_ok(const ShapeDev& sh) { return sweep_stream_ok(sh) && sh.L2 == kHelpCols; }
 
 template <bool kE, bool kAnti>
-static hipError_t launch_helped_one(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st,
+static hipError_t launch_helped_one(const ShapeDev& sh, uint64_t seed, When t, hipStream_t st,
                                     bool launch) {
     static size_t lds_set = 0;
     const size_t lds = (size_t)helped_words(sh) * 8;
     hipError_t e = allow_lds((const void*)k_sweep_helped<kE, kAnti>, lds, lds_set);
     if (e != hipSuccess || !launch) return e;
     hipLaunchKernelGGL((k_sweep_helped<kE, kAnti>), dim3(sh.R * sh.nk * sh.W), dim3(kHelpedThreads), lds, st,
-                       sh, (uint32_t)seed, (uint32_t)(seed >> 32), ctr);
+                       sh, (uint32_t)seed, (uint32_t)(seed >> 32), t);
     return hipGetLastError();
 }
 
 template <bool kE>
-static hipError_t launch_helped_bc(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st,
+static hipError_t launch_helped_bc(const ShapeDev& sh, uint64_t seed, When t, hipStream_t st,
                                    bool launch) {
-    return sh.apm ? launch_helped_one<kE, true>(sh, seed, ctr, st, launch)
-                  : launch_helped_one<kE, false>(sh, seed, ctr, st, launch);
+    return sh.apm ? launch_helped_one<kE, true>(sh, seed, t, st, launch)
+                  : launch_helped_one<kE, false>(sh, seed, t, st, launch);
 }
 
-hipError_t launch_sweep_helped(const ShapeDev& sh, uint64_t seed, const Counters* ctr, bool energy,
+hipError_t launch_sweep_helped(const ShapeDev& sh, uint64_t seed, When t, bool energy,
                                hipStream_t st) {
-    return energy ? launch_helped_bc<true>(sh, seed, ctr, st, true)
-                  : launch_helped_bc<false>(sh, seed, ctr, st, true);
+    return energy ? launch_helped_bc<true>(sh, seed, t, st, true)
+                  : launch_helped_bc<false>(sh, seed, t, st, true);
 }
 
 hipError_t prepare_sweep_helped(const ShapeDev& sh, bool energy) {
-    return energy ? launch_helped_bc<true>(sh, 0, nullptr, nullptr, false)
-                  : launch_helped_bc<false>(sh, 0, nullptr, nullptr, false);
+    return energy ? launch_helped_bc<true>(sh, 0, When{0, nullptr}, nullptr, false)
+                  : launch_helped_bc<false>(sh, 0, When{0, nullptr}, nullptr, false);
 }
 
-hipError_t launch_sweep_stream(const ShapeDev& sh, uint64_t seed, const Counters* ctr,
+hipError_t launch_sweep_stream(const ShapeDev& sh, uint64_t seed, When t,
                                bool energy, int occ, hipStream_t st) {
     if (occ >= 5)
-        return energy ? launch_bc<true, 5>(sh, seed, ctr, st) : launch_bc<false, 5>(sh, seed, ctr, st);
-    return energy ? launch_bc<true, 1>(sh, seed, ctr, st) : launch_bc<false, 1>(sh, seed, ctr, st);
+        return energy ? launch_bc<true, 5>(sh, seed, t, st) : launch_bc<false, 5>(sh, seed, t, st);
+    return energy ? launch_bc<true, 1>(sh, seed, t, st) : launch_bc<false, 1>(sh, seed, t, st);
 }
 
 static const void* batch_fn(int occ, bool anti) {

@@ -56,6 +56,14 @@ struct Counters {
     uint32_t pad;
 };
 
+// A sweep's counter t: the value itself, or (launches captured in a graph) read
+// on the device from the shape's counters.
+struct When {
+    uint32_t value;
+    const Counters* ctr;  // nullptr: value
+    __device__ __forceinline__ uint32_t get() const { return ctr ? ctr->t : value; }
+};
+
 // Work queue of the persistent batched sweep; zero between launches.
 struct BatchQueue {
     uint32_t next;  // next work item to hand out
@@ -227,19 +235,23 @@ hipError_t launch_mask_rebuild(const ShapeDev& sh, hipStream_t st);
 // variant 0: streaming kernel (needs bucket tables), 1: chunked kernel,
 // 2: streaming kernel compiled for >= 5 waves per SIMD, 3: streaming kernel
 // with helper waves where L^2 = 576 (else as 0).
-// energy: also recount U (the chunked kernel always does).
-hipError_t launch_sweep(const ShapeDev& sh, uint64_t seed, const Counters* ctr, int variant,
-                        bool energy, hipStream_t st);
-hipError_t launch_sweep_stream(const ShapeDev& sh, uint64_t seed, const Counters* ctr,
-                               bool energy, int occ, hipStream_t st);
+// energy: also recount U (the chunked kernel always does).  ncu: compute
+// units of the device (few configurations are swept in parts, variants 0, 3).
+hipError_t launch_sweep(const ShapeDev& sh, uint64_t seed, When t, int variant, bool energy, int ncu,
+                        hipStream_t st);
+hipError_t launch_sweep_stream(const ShapeDev& sh, uint64_t seed, When t, bool energy, int occ, hipStream_t st);
 // Kernel attributes a later launch of this shape and variant needs (dynamic
 // LDS above 64 KiB), set outside any stream capture.
-hipError_t prepare_sweep(const ShapeDev& sh, int variant, bool energy);
+hipError_t prepare_sweep(const ShapeDev& sh, int variant, bool energy, int ncu);
+// A sweep in parts along tau (nparts >= 2 from sweep_parts): the parts, then
+// the sites at their boundaries.
+int sweep_parts(const ShapeDev& sh, bool energy, int ncu);
+hipError_t launch_sweep_parts(const ShapeDev& sh, uint64_t seed, When t, bool energy, int nparts, hipStream_t st,
+                              bool launch = true);
 hipError_t prepare_sweep_stream(const ShapeDev& sh, bool energy, int occ);
 // Helper-wave form of the streaming sweep (L^2 = 576 only).
 bool sweep_helped_ok(const ShapeDev& sh);
-hipError_t launch_sweep_helped(const ShapeDev& sh, uint64_t seed, const Counters* ctr, bool energy,
-                               hipStream_t st);
+hipError_t launch_sweep_helped(const ShapeDev& sh, uint64_t seed, When t, bool energy, hipStream_t st);
 hipError_t prepare_sweep_helped(const ShapeDev& sh, bool energy);
 bool sweep_stream_ok(const ShapeDev& sh);
 // LDS of a streaming-sweep block of `teams` configurations and `threads`
@@ -260,8 +272,12 @@ hipError_t launch_sweep_batch(const BatchArgs& a, int occ, bool anti, int blocks
 // counter advance t += 1, m += due.
 hipError_t launch_temper_batch(const TemperBatchArgs& a, int blocks, int max_nk, hipStream_t st);
 hipError_t launch_advance_batch(const TemperBatchArgs& a, hipStream_t st);
-hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st);
-hipError_t launch_advance(Counters* ctr, uint32_t dt, uint32_t dm, hipStream_t st);
+hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st);
+// Counters of the first n <= 64 shapes set to the given values.
+struct CounterValues {
+    uint32_t t[64], m[64];
+};
+hipError_t launch_set_counters(Counters* ctr, const CounterValues& v, int n, hipStream_t st);
 // Measurement of configurations cfg0 .. cfg0+ncfg-1 (cfg = i*S + s) into the
 // records (which must be zeroed first).  mode 0: batched int8-MFMA kernels;
 // mode 1: plain per-sample VALU form, one launch per configuration.
@@ -309,8 +325,8 @@ hipError_t plain_init_spins(const ShapeDev& sh, uint64_t seed, hipStream_t st);
 hipError_t plain_labels_identity(const ShapeDev& sh, hipStream_t st);
 hipError_t plain_energy(const ShapeDev& sh, hipStream_t st);
 // colour 0, colour 1 and the energy recount of one sweep
-hipError_t plain_sweep(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st);
-hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, const Counters* ctr, hipStream_t st);
+hipError_t plain_sweep(const ShapeDev& sh, uint64_t seed, uint32_t t, hipStream_t st);
+hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st);
 bool plain_measure_ok(const ShapeDev& sh);
 // pair records of configurations cfg0 .. cfg0+ncfg-1 (zeroed first)
 hipError_t plain_measure(const ShapeDev& sh, int cfg0, int ncfg, hipStream_t st);
