@@ -18,6 +18,8 @@
 //
 // Kernels reuse ShapeDev: W holds the number of samples ns, S and J point at
 // the int8 arrays.
+#include <algorithm>
+
 #include "tfim_internal.h"
 
 namespace tfim {
@@ -111,10 +113,107 @@ __global__ void __launch_bounds__(256) k_plain_half(ShapeDev sh, uint32_t key0, 
     }
 }
 
+// n sweeps of a configuration that fits in LDS, one workgroup each: the spins
+// stay in LDS from the first sweep to the last (tempering, which needs U and
+// other configurations, ends a run), U is counted once at the end.  The same
+// numbers and the same order of colours as k_plain_half.  Bound by the latency
+// of a half-sweep, a Philox call between two barriers.  A unit (a column's
+// eight planes) reads all its neighbours before the call and decides its four
+// sites after it: sites of one colour are no neighbours.  kOne: a unit per
+// thread, whose place and couplings then stay in registers.
+// L = 8, Ltau = 32, two configurations: 14 us per sweep in three launches
+// (two half-sweeps and a recount) -> 2.1; 2048 configurations of L = 16,
+// Ltau = 216 with tempering at every sweep 2.2 ms per sweep -> 0.9.
+constexpr size_t kPlainLds = 63 * 1024;  // spins and columns of a configuration
+constexpr int kPlainRunThreads = 1024;
+
+// a column's neighbours (offsets in a plane) and couplings
+struct PlainCol {
+    uint16_t xm, xp, ym, yp;
+    int8_t jxm, jxp, jym, jyp;
+    int odd;  // (x + y) & 1
+};
+
+__host__ __device__ inline size_t plain_run_lds(const ShapeDev& sh) {
+    return (size_t)sh.L2 * (sh.Lt + sizeof(PlainCol));
+}
+
+template <bool kOne>
+__global__ void __launch_bounds__(kPlainRunThreads)
+k_plain_run(ShapeDev sh, uint32_t key0, uint32_t key1, uint32_t t0, uint32_t n) {
+    extern __shared__ __align__(16) char lds[];  // [L2] columns, [Ltau][L2] spins
+    __shared__ uint32_t tot;
+    const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W;
+    const int cfg = blockIdx.x;  // (r*nk + w)*ns + s
+    const int s = cfg % ns, rw = cfg / ns, r = rw / nk, w = rw % nk;
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    PlainCol* const col = (PlainCol*)lds;
+    int8_t* const sp = (int8_t*)(col + L2);
+    int* const cf = (int*)((int8_t*)sh.S + (size_t)cfg * L2 * Lt);  // L2 is a multiple of 4
+    for (int e = tid; e < L2 * Lt / 4; e += nthr) ((int*)sp)[e] = cf[e];
+    const int8_t* const J = (const int8_t*)sh.J + (size_t)s * 2 * L2;
+    for (int e = tid; e < L2; e += nthr) {
+        const int x = e % L, y = e / L;
+        const int xm = (x ? x - 1 : L - 1) + L * y, xp = (x + 1 < L ? x + 1 : 0) + L * y;
+        const int ym = x + L * (y ? y - 1 : L - 1), yp = x + L * (y + 1 < L ? y + 1 : 0);
+        col[e] = PlainCol{(uint16_t)xm, (uint16_t)xp, (uint16_t)ym, (uint16_t)yp,
+                          J[xm],        J[e],         J[L2 + ym],   J[L2 + e], (x + y) & 1};
+    }
+    if (tid == 0) tot = 0;
+    const uint32_t* const Tu = sh.Tu + 3 * sh.kidx[((size_t)r * ns + s) * nk + w];
+    const uint32_t T0 = Tu[0], T1 = Tu[1], T2 = Tu[2];
+    const uint32_t c3 = ctr_word3(plain_word(sh, s), sh.sid, kTagMetro);
+    const int sgn = sh.apm ? -1 : 1, units = L2 * ((Lt + 7) / 8);
+    __syncthreads();
+    auto update = [&](const PlainCol& cl, int xy, int e, uint32_t t, int c) {
+        const int tau0 = 8 * (e / L2) + ((c + cl.odd) & 1);
+        int h[4], sv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int tau = min(tau0 + 2 * i, Lt - 1);  // past the end: read, not used
+            const int8_t* const P = sp + tau * L2;
+            const int dn = tau == 0 ? sgn * sp[(Lt - 1) * L2 + xy] : P[xy - L2];
+            const int up = tau == Lt - 1 ? sgn * sp[xy] : P[xy + L2];
+            h[i] = cl.jxp * P[cl.xp] + cl.jxm * P[cl.xm] + cl.jyp * P[cl.yp] + cl.jym * P[cl.ym] + dn + up;
+            sv[i] = P[xy];
+        }
+        const U4 o = philox10((uint32_t)e, t, ((uint32_t)rw << 1) | (uint32_t)c, c3, key0, key1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int dE = 2 * sv[i] * h[i];
+            const bool acc = dE <= 0 || o.v[i] < (dE == 12 ? T0 : (dE == 8 ? T1 : T2));
+            if (tau0 + 2 * i < Lt && acc) sp[(tau0 + 2 * i) * L2 + xy] = (int8_t)-sv[i];
+        }
+    };
+    const int xy0 = tid % L2;
+    const PlainCol one = col[xy0];
+    for (uint32_t k = 0; k < n; ++k)
+        for (int c = 0; c < 2; ++c) {
+            if constexpr (kOne) {
+                if (tid < units) update(one, xy0, tid, t0 + k, c);
+            } else {
+                for (int e = tid; e < units; e += nthr) update(col[e % L2], e % L2, e, t0 + k, c);
+            }
+            __syncthreads();
+        }
+    uint32_t u = 0;
+    for (int e = tid; e < L2 * Lt; e += nthr) {
+        const int tau = e / L2, xy = e - tau * L2;
+        const PlainCol cl = col[xy];
+        const int8_t* const P = sp + tau * L2;
+        const int sv = P[xy], up = tau == Lt - 1 ? sgn * sp[xy] : P[xy + L2];
+        u += (cl.jxp * sv * P[cl.xp] < 0) + (cl.jyp * sv * P[cl.yp] < 0) + (sv * up < 0);
+    }
+    atomicAdd(&tot, u);
+    for (int e = tid; e < L2 * Lt / 4; e += nthr) cf[e] = ((const int*)sp)[e];
+    __syncthreads();
+    if (tid == 0) sh.U[((size_t)r * ns + s) * nk + w] = tot;
+}
+
 // Unsatisfied bonds U of every configuration from the action: each site
 // counts its +x, +y and +tau bonds (E = 2U - 3N).  One workgroup per
 // configuration.
-__global__ void __launch_bounds__(256) k_plain_energy(ShapeDev sh) {
+__global__ void __launch_bounds__(1024) k_plain_energy(ShapeDev sh) {
     __shared__ uint32_t tot;
     const int8_t* S8 = (const int8_t*)sh.S;
     const int8_t* J = (const int8_t*)sh.J;
@@ -127,6 +226,7 @@ __global__ void __launch_bounds__(256) k_plain_energy(ShapeDev sh) {
     if (threadIdx.x == 0) tot = 0;
     __syncthreads();
     uint32_t u = 0;
+#pragma unroll 4
     for (int lin = threadIdx.x; lin < L2 * Lt; lin += blockDim.x) {
         const int xy = lin % L2, tau = lin / L2;
         const int x = xy % L, y = xy / L;
@@ -192,27 +292,27 @@ __global__ void k_plain_zero(int64_t* p, size_t n) {
 
 constexpr int kPlainMaxP = 15;  // six replicas
 
-// Pair records of configuration cfg = cfg0 + blockIdx.y (k-index i, sample s):
+// Pair records of configuration cfg = cfg0 + blockIdx.y (k-index i, sample s),
+// blocks [0, gx) of x:
 // G^r_xy = sum_tau S^r_x,tau S^r_y,tau of the walker at k-index i of every
 // replica, one element (x, y) per thread, int32; D_x[d] += G^a_xy G^b_xy at
 // d = (x1 - y1) mod L (D_y in x2 - y2), in int64.
-__global__ void __launch_bounds__(256) k_plain_gram(ShapeDev sh, int cfg0) {
-    __shared__ unsigned long long D[kPlainMaxP * 2 * 24];
+__device__ __forceinline__ void plain_gram_block(const ShapeDev& sh, int cfg, int bx, int nbx,
+                                                 unsigned long long* D) {
     const int8_t* S8 = (const int8_t*)sh.S;
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W, R = sh.R, P = sh.P;
-    const int cfg = cfg0 + blockIdx.y;
     const int i = cfg / ns, s = cfg % ns;
     for (int e = threadIdx.x; e < P * 2 * L; e += blockDim.x) D[e] = 0;
     __syncthreads();
-    const long long nel = (long long)L2 * L2;
-    for (long long el = (long long)blockIdx.x * blockDim.x + threadIdx.x; el < nel;
-         el += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(el / L2), y = (int)(el % L2);
+    const int nel = L2 * L2;
+    for (int el = bx * (int)blockDim.x + threadIdx.x; el < nel; el += nbx * (int)blockDim.x) {
+        const int x = el / L2, y = el % L2;
         int G[6];
         for (int r = 0; r < R; ++r) {
             const int w = sh.winv[((size_t)r * ns + s) * nk + i];
             const int8_t* cf = S8 + ((size_t)(r * nk + w) * ns + s) * L2 * Lt;
             int acc = 0;
+#pragma unroll 4
             for (int tau = 0; tau < Lt; ++tau) acc += cf[(size_t)tau * L2 + x] * cf[(size_t)tau * L2 + y];
             G[r] = acc;
         }
@@ -231,39 +331,73 @@ __global__ void __launch_bounds__(256) k_plain_gram(ShapeDev sh, int cfg0) {
         if (D[e]) atomicAdd((unsigned long long*)&sh.rec[((size_t)cfg * P + e / (2 * L)) * rl + e % (2 * L)], D[e]);
 }
 
-// Overlap part of the pair records: Q^ab_t1,t2 = sum_x S^a_x,t1 S^b_x,t2, one
-// element per thread; trQ, sum Q^2, sum Q^4 in int64 (|Q| <= L^2).
-__global__ void __launch_bounds__(256) k_plain_overlap(ShapeDev sh, int cfg0) {
-    __shared__ unsigned long long red[kPlainMaxP * 3];
-    const int8_t* S8 = (const int8_t*)sh.S;
-    const int L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W, R = sh.R, P = sh.P;
-    const int cfg = cfg0 + blockIdx.y;
+// Overlap part of the pair records, the other blocks of x:
+// Q^ab_t1,t2 = sum_x S^a_x,t1 S^b_x,t2, four sites in a dword (L^2 is a
+// multiple of 4), one element per thread; trQ, sum Q^2, sum Q^4 in int64
+// (|Q| <= L^2).
+__device__ __forceinline__ void plain_overlap_block(const ShapeDev& sh, int cfg, int bx, int nbx,
+                                                    unsigned long long* red) {
+    const int n4 = sh.L2 / 4, Lt = sh.Lt, nk = sh.nk, ns = sh.W, R = sh.R, P = sh.P;
+    const int* S4 = (const int*)sh.S;
     const int i = cfg / ns, s = cfg % ns;
     for (int e = threadIdx.x; e < P * 3; e += blockDim.x) red[e] = 0;
     __syncthreads();
-    const long long nel = (long long)Lt * Lt;
-    for (long long el = (long long)blockIdx.x * blockDim.x + threadIdx.x; el < nel;
-         el += (long long)gridDim.x * blockDim.x) {
-        const int t1 = (int)(el / Lt), t2 = (int)(el % Lt);
-        int p = 0;
-        for (int a = 0; a < R; ++a)
-            for (int b = a + 1; b < R; ++b, ++p) {
-                const int wa = sh.winv[((size_t)a * ns + s) * nk + i];
-                const int wb = sh.winv[((size_t)b * ns + s) * nk + i];
-                const int8_t* pa = S8 + (((size_t)(a * nk + wa) * ns + s) * Lt + t1) * L2;
-                const int8_t* pb = S8 + (((size_t)(b * nk + wb) * ns + s) * Lt + t2) * L2;
+    const unsigned step = (unsigned)nbx * blockDim.x, first = (unsigned)bx * blockDim.x + threadIdx.x;
+    const unsigned d1 = step / (unsigned)Lt, d2 = step % (unsigned)Lt;
+    int p = 0;
+    for (int a = 0; a < R; ++a)
+        for (int b = a + 1; b < R; ++b, ++p) {
+            const int wa = sh.winv[((size_t)a * ns + s) * nk + i];
+            const int wb = sh.winv[((size_t)b * ns + s) * nk + i];
+            const int* const ca = S4 + ((size_t)(a * nk + wa) * ns + s) * Lt * n4;
+            const int* const cb = S4 + ((size_t)(b * nk + wb) * ns + s) * Lt * n4;
+            long long m0 = 0, m1 = 0, m2 = 0;
+            unsigned t1 = first / (unsigned)Lt, t2 = first % (unsigned)Lt;
+            while (t1 < (unsigned)Lt) {
+                const int* const pa = ca + (size_t)t1 * n4;
+                const int* const pb = cb + (size_t)t2 * n4;
                 int q = 0;
-                for (int x = 0; x < L2; ++x) q += pa[x] * pb[x];
+#pragma unroll 4
+                for (int x = 0; x < n4; ++x) q = __builtin_amdgcn_sdot4(pa[x], pb[x], q, false);
                 const long long q2 = (long long)q * q;
-                atomicAdd(&red[p * 3 + 1], (unsigned long long)q2);
-                atomicAdd(&red[p * 3 + 2], (unsigned long long)(q2 * q2));
-                if (t1 == t2) atomicAdd(&red[p * 3 + 0], (unsigned long long)(long long)q);
+                m1 += q2;
+                m2 += q2 * q2;
+                if (t1 == t2) m0 += q;
+                t1 += d1;
+                t2 += d2;
+                if (t2 >= (unsigned)Lt) {
+                    t2 -= Lt;
+                    ++t1;
+                }
             }
-    }
+            for (int o = 32; o; o >>= 1) {
+                m0 += __shfl_xor(m0, o);
+                m1 += __shfl_xor(m1, o);
+                m2 += __shfl_xor(m2, o);
+            }
+            if ((threadIdx.x & 63) == 0) {
+                atomicAdd(&red[p * 3], (unsigned long long)m0);
+                atomicAdd(&red[p * 3 + 1], (unsigned long long)m1);
+                atomicAdd(&red[p * 3 + 2], (unsigned long long)m2);
+            }
+        }
     __syncthreads();
     const int rl = 2 * sh.L + 3;
     for (int e = threadIdx.x; e < P * 3; e += blockDim.x)
         if (red[e]) atomicAdd((unsigned long long*)&sh.rec[((size_t)cfg * P + e / 3) * rl + 2 * sh.L + e % 3], red[e]);
+}
+
+// Both parts in one launch, with eight loads in flight per thread: bound by
+// the latency of the loads (L = 8, Ltau = 32, one configuration: two launches
+// of 16 and 15 us with a load at a time -> one of 8; 2048 configurations of
+// L = 16, Ltau = 216 49 ms -> 3).
+__global__ void __launch_bounds__(256) k_plain_records(ShapeDev sh, int cfg0, int gx) {
+    __shared__ unsigned long long sums[kPlainMaxP * 2 * 24];
+    const int cfg = cfg0 + blockIdx.y;
+    if ((int)blockIdx.x < gx)
+        plain_gram_block(sh, cfg, blockIdx.x, gx, sums);
+    else
+        plain_overlap_block(sh, cfg, blockIdx.x - gx, gridDim.x - gx, sums);
 }
 
 // A[i][h][d] = sum over samples and pairs of the records' D_x (h = 0), D_y (h = 1).
@@ -309,18 +443,31 @@ hipError_t plain_labels_identity(const ShapeDev& sh, hipStream_t st) {
 }
 
 hipError_t plain_energy(const ShapeDev& sh, hipStream_t st) {
-    hipLaunchKernelGGL(k_plain_energy, dim3(sh.R * sh.nk * sh.W), dim3(256), 0, st, sh);
+    hipLaunchKernelGGL(k_plain_energy, dim3(sh.R * sh.nk * sh.W), dim3(std::min(1024, (sh.L2 * sh.Lt + 63) / 64 * 64)), 0, st, sh);
     return hipGetLastError();
 }
 
-hipError_t plain_sweep(const ShapeDev& sh, uint64_t seed, uint32_t t, hipStream_t st) {
+hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, hipStream_t st) {
     const size_t total = (size_t)sh.R * sh.nk * sh.W * sh.L2 * ((sh.Lt + 7) / 8);
-    for (int c = 0; c < 2; ++c) {
-        hipLaunchKernelGGL(k_plain_half, dim3(grid_of(total)), dim3(256), 0, st, sh, (uint32_t)seed,
-                           (uint32_t)(seed >> 32), t, c);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    const int units = sh.L2 * ((sh.Lt + 7) / 8), ncfg = sh.R * sh.nk * sh.W;
+    // A workgroup per configuration, unless a run of several sweeps goes over
+    // few large ones.  20 sweeps and a read-back at L = 16, Ltau = 216 (6912
+    // units): two configurations 710 us against 505 over the whole chip, but 64
+    // of them 949 against 1694, and two with tempering at every sweep 1222
+    // against 1339; two of Ltau = 64 (2048 units) 279 against 427.
+    if (plain_run_lds(sh) <= kPlainLds && (units <= 4 * kPlainRunThreads || ncfg > 8 || n == 1)) {
+        const int threads = std::min(kPlainRunThreads, (units + 63) / 64 * 64);
+        hipLaunchKernelGGL(units <= threads ? k_plain_run<true> : k_plain_run<false>, dim3(sh.R * sh.nk * sh.W),
+                           dim3(threads), plain_run_lds(sh), st, sh, (uint32_t)seed, (uint32_t)(seed >> 32), t, n);
+        return hipGetLastError();
     }
+    for (uint32_t k = 0; k < n; ++k)
+        for (int c = 0; c < 2; ++c) {
+            hipLaunchKernelGGL(k_plain_half, dim3(grid_of(total)), dim3(256), 0, st, sh, (uint32_t)seed,
+                               (uint32_t)(seed >> 32), t + k, c);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
     return plain_energy(sh, st);
 }
 
@@ -344,10 +491,7 @@ hipError_t plain_measure(const ShapeDev& sh, int cfg0, int ncfg, hipStream_t st)
         const int n = ncfg - c < 65535 ? ncfg - c : 65535;
         const unsigned gx = grid_of((size_t)sh.L2 * sh.L2, 64);
         const unsigned gq = grid_of((size_t)sh.Lt * sh.Lt, 256);
-        hipLaunchKernelGGL(k_plain_gram, dim3(gx, n), dim3(256), 0, st, sh, cfg0 + c);
-        e = hipGetLastError();
-        if (e != hipSuccess) break;
-        hipLaunchKernelGGL(k_plain_overlap, dim3(gq, n), dim3(256), 0, st, sh, cfg0 + c);
+        hipLaunchKernelGGL(k_plain_records, dim3(gx + gq, n), dim3(256), 0, st, sh, cfg0 + c, (int)gx);
         e = hipGetLastError();
     }
     return e;

@@ -584,9 +584,7 @@ static hipError_t timing_end(tfim_plan* pl, std::pair<hipEvent_t, hipEvent_t>& e
 static hipError_t timed_sweep(tfim_plan* pl, int i, bool energy) {
     std::pair<hipEvent_t, hipEvent_t> ev;
     hipError_t e = timing_begin(pl, ev);
-    if (e == hipSuccess && plain(pl))
-        e = tfim::plain_sweep(dev_of(pl, i), pl->seed, (uint32_t)pl->t[i], pl->stream);
-    else if (e == hipSuccess)
+    if (e == hipSuccess)
         e = tfim::launch_sweep(dev_of(pl, i), pl->seed, tfim::When{(uint32_t)pl->t[i], nullptr}, pl->variant, energy,
                                pl->n_cu, pl->stream);
     return timing_end(pl, ev, 1, e);
@@ -613,6 +611,33 @@ static hipError_t enqueue_sweep(tfim_plan* pl, bool last) {
         const uint32_t pe = pl->shapes[i].s.pt_every;
         const bool due = pe > 0 && ((pl->t[i] + 1) % pe) == 0;
         if (due) e = temper(pl, i);
+    }
+    pl->counters_behind = true;
+    return e;
+}
+
+// n sweeps of every shape of a plain plan: shape by shape, in runs that end
+// where a tempering step is due (only then, and at the end, is U needed).
+static hipError_t enqueue_plain(tfim_plan* pl, uint64_t n) {
+    hipError_t e = hipSuccess;
+    for (size_t i = 0; i < pl->shapes.size() && e == hipSuccess; ++i) {
+        const uint64_t pe = pl->shapes[i].s.pt_every, end = pl->t[i] + n;
+        while (pl->t[i] < end && e == hipSuccess) {
+            // at most 2^12 sweeps in a launch (tens of ms)
+            uint64_t run = std::min<uint64_t>(end - pl->t[i], 1u << 12);
+            if (pe > 0) run = std::min(run, pe - pl->t[i] % pe);
+            std::pair<hipEvent_t, hipEvent_t> ev;
+            e = timing_begin(pl, ev);
+            if (e == hipSuccess)
+                e = tfim::plain_sweeps(dev_of(pl, (int)i), pl->seed, (uint32_t)pl->t[i], (uint32_t)run, pl->stream);
+            e = timing_end(pl, ev, (uint32_t)run, e);
+            if (e != hipSuccess) break;
+            pl->t[i] += run;
+            if (pe > 0 && pl->t[i] % pe == 0) {
+                e = temper(pl, (int)i);
+                pl->m[i] += 1;
+            }
+        }
     }
     pl->counters_behind = true;
     return e;
@@ -870,6 +895,8 @@ static tfim_status sweep_impl(tfim_plan* pl, uint64_t n) {
     if (pl->schedule == TFIM_SCHED_BATCHED || pl->schedule == TFIM_SCHED_CONCURRENT) {
         e = enqueue_batched(pl, n);
         if (e == hipSuccess) advance(n);
+    } else if (plain(pl)) {
+        e = enqueue_plain(pl, n);
     } else {
         for (uint64_t s = 0; s < n && e == hipSuccess; ++s) {
             e = enqueue_sweep(pl, s + 1 == n);  // reads the mirrors of this sweep

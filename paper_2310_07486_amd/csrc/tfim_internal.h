@@ -324,8 +324,8 @@ hipError_t plain_init_couplings(const ShapeDev& sh, uint64_t seed, hipStream_t s
 hipError_t plain_init_spins(const ShapeDev& sh, uint64_t seed, hipStream_t st);
 hipError_t plain_labels_identity(const ShapeDev& sh, hipStream_t st);
 hipError_t plain_energy(const ShapeDev& sh, hipStream_t st);
-// colour 0, colour 1 and the energy recount of one sweep
-hipError_t plain_sweep(const ShapeDev& sh, uint64_t seed, uint32_t t, hipStream_t st);
+// n >= 1 sweeps t, t + 1, .. and the energy recount after the last
+hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, hipStream_t st);
 hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st);
 bool plain_measure_ok(const ShapeDev& sh);
 // pair records of configurations cfg0 .. cfg0+ncfg-1 (zeroed first)

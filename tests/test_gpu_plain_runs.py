@@ -1,0 +1,40 @@
+"""Plain-form sweeps: a configuration in one workgroup's LDS for a run of sweeps,
+or a launch per half-sweep over the whole chip; both against the oracle at the
+sizes between which the choice lies."""
+import numpy as np
+import pytest
+
+from oracle import measure as om
+from paper_2310_07486_amd import tfim
+from paper_2310_07486_amd.workloads import Shape, ladder
+from test_gpu_plain import PLAIN, _chain, _say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,Lt,ns,nk,pt,bc", [
+    (6, 30, 2, 2, 0, 1),     # one unit a thread, a part wavefront, ragged chunk of tau
+    (8, 128, 2, 2, 2, 0),    # exactly 1024 units
+    (8, 130, 1, 2, 3, 1),    # the first with two units a thread
+    (16, 130, 1, 1, 0, 1),   # 4352 units, few configurations: half-sweep launches
+    (16, 130, 1, 2, 1, 0),   # the same in runs of one sweep: LDS
+    (16, 130, 3, 2, 4, 0),   # the same with 12 configurations: LDS
+    (16, 236, 1, 2, 5, 0),   # the largest Ltau in LDS at this L (64512 bytes)
+    (16, 238, 1, 2, 1, 0),   # one beyond it
+])
+def test_runs_of_sweeps(L, Lt, ns, nk, pt, bc):
+    sh = Shape(L, Lt, ns, 2, ladder(0.22, 0.4, nk), pt_every=pt, stream_id=3, word_offset=1, bc_tau=bc)
+    _say(f"plain runs L={L} Lt={Lt} samples={ns} nk={nk} pt={pt} bc={bc}")
+    plan = tfim.Plan([sh], 77, form=PLAIN)
+    plan.init()
+    ch = _chain(sh, 77, list(range(ns)))
+    for n in (1, 4, 2):
+        plan.sweep(n)
+        ch.run(n)
+        kidx, U = plan.get_state(0)
+        assert np.array_equal(plan.export_spins(0), ch.S), "spins differ"
+        assert np.array_equal(kidx, ch.kidx), "k labels differ"
+        assert np.array_equal(U, ch.U), "energies differ"
+    assert plan.counters() == (7, 7 // pt if pt else 0)
+    assert np.array_equal(plan.measure(0, tfim.TFIM_MEASURE_RECORDS), om.measure_chain(ch))
+    plan.close()
