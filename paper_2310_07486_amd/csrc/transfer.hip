@@ -11,16 +11,14 @@
 //   T = D^1/2 K D^1/2,  D = diag(exp(k E0)),  K = (x)_x [[e^k, e^-k], [e^-k, e^k]],
 // on 2^N states (N = L^2; bit x of the index is set when s_x = -1).  K is
 // applied as N two-term butterflies, one per bit: w[s] <- e^k w[s] +
-// e^-k w[s ^ 2^x].  For N >= 16 every pass works on tiles of 4096 states (32
-// KB of LDS): the first on bits 0..11 of contiguous chunks (and the D^1/2
-// scale on the way in), the others on up to 8 bits with 16 to 256 columns
-// of consecutive lower indices (128-byte or longer rows), in place, the last
-// one scaling by D^1/2 on the way out.  Each thread applies four butterflies
-// at a time in registers between LDS exchanges.  N <= 12 (L = 2, 3) takes
-// one block per 2^N states.  E0(s) comes from popcounts of s xor its
-// neighbour-permuted copies against the masks of the +1 and -1 couplings;
-// exp(k E0 / 2) is a table of 4N + 1 entries.  The product is HBM-bound:
-// each pass reads and writes the whole vector (three passes at L = 5).
+// e^-k w[s ^ 2^x].  L = 5: two passes over the vector, on tiles of 2^14 states
+// in registers (k_tm_half).  L = 4: tiles of 4096 states (32 KB of LDS), first
+// on bits 0..11 of contiguous chunks (and the D^1/2 scale on the way in), then
+// in place on the other 4 bits with columns of 256 consecutive lower indices,
+// scaling by D^1/2 on the way out.  N <= 12 (L = 2, 3) takes one block per 2^N
+// states.  E0(s) comes from popcounts of s xor its neighbour-permuted copies
+// against the masks of the +1 and -1 couplings; exp(k E0 / 2) is a table of
+// 4N + 1 entries.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -31,7 +29,6 @@ namespace tfim {
 namespace {
 
 constexpr int kLowBits = 12;   // bits of the first pass (4096 states per block)
-constexpr int kMidBits = 8;    // bits per later pass
 constexpr int kMaxN = 25;      // L <= 5
 
 struct TmParams {
@@ -664,6 +661,117 @@ __global__ void __launch_bounds__(512) k_tm_power16(TmPower A) {
     if (tid == 0) *A.state = st;
 }
 
+// ---------------------------------------------------------------------------
+// The product of L = 5 in two passes, 14 bits and 11
+//
+// Tiles of 2^14 states in the registers of 512 threads, 32 each: the first
+// pass on bits 0..13 of contiguous states, with D^1/2 on the way in, the second
+// in place on bits 14..24 of 8 columns (64-byte rows), with D^1/2 on the way
+// out.  By positions p (p0 = slot 0, p1..p9 = the thread,
+// p10..p13 = slots 1..4; the second pass's p0..p2 are its columns): slots first,
+// an exchange through 64 KB of LDS in two rounds (by p0) of lane 2 and the
+// waves against slots 1..4, lanes 5 and 4 swapped with slots 1 and 2, the other
+// lanes by data-parallel moves.  Two workgroups per CU, one's loads under the
+// other's arithmetic.  Bound by memory, a read and a write of the vector per
+// pass: three passes of 12 + 8 + 5 bits took 326 us at L = 5, these 103 + 128
+// (copy rate: 107 each).  The butterflies keep both factors: with e^k taken out
+// the error of a product against 64 bits grew from 1.3e-16 to 7.6e-16, for 5 us.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void swap_lane4(double& x, double& y) {
+    const uint64_t a = __builtin_bit_cast(uint64_t, x), b = __builtin_bit_cast(uint64_t, y);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    x = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]);
+    y = __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+typedef double Pair8 __attribute__((ext_vector_type(2), aligned(8)));  // vectors come 8-byte aligned
+
+template <bool kHigh>
+__global__ void __launch_bounds__(512, 4) k_tm_half(TmParams P, const double* in, double* out) {
+    __shared__ double sh[1 << 13];
+    __shared__ double dt[4 * kMaxN + 1];
+    const int tid = threadIdx.x;
+    // 32 neighbouring tiles (2 KB of a row) on an XCD at a time, the XCDs side by
+    // side: the tiles in flight cover the channels and share lines.  Second pass
+    // 20 us longer with 16 KB to an XCD, 8 with 512 bytes.
+    const uint32_t xcd = blockIdx.x & 7, j0 = blockIdx.x >> 3;
+    const uint32_t tile = kHigh ? (j0 & ~31u) << 3 | xcd << 5 | (j0 & 31) : blockIdx.x;
+    const double a = P.a, b = P.b;
+    // positions to index bits
+    auto spread = [](uint32_t p) { return kHigh ? (p & 7) | (p & ~7u) << 11 : p; };
+    const uint32_t base = tile << (kHigh ? 3 : 14);
+    auto bit = [&](int j) { return (uint32_t)(tid >> j) & 1; };
+    for (int e = tid; e < 4 * P.N + 1; e += 512) dt[e] = P.dtab[e];
+    double r[32];
+    const uint32_t s0 = base + spread((uint32_t)tid << 1);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const Pair8 v = *(const Pair8*)(in + s0 + spread((uint32_t)e << 10));
+        r[2 * e] = v.x;
+        r[2 * e + 1] = v.y;
+    }
+    if (!kHigh) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 32; ++i) r[i] *= half_diag(P, s0 + ((uint32_t)(i >> 1) << 10) + (i & 1), dt);
+    }
+    auto slot = [&](int j) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i)
+            if (!(i & (1 << j))) {
+                const double x0 = r[i], x1 = r[i | (1 << j)];
+                r[i] = a * x0 + b * x1;
+                r[i | (1 << j)] = b * x0 + a * x1;
+            }
+    };
+#pragma unroll
+    for (int j = kHigh ? 1 : 0; j < 5; ++j) slot(j);
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        if (!kHigh) {
+            r[i] = a * r[i] + b * dpp_mov<0xB1>(r[i]);  // quad_perm 1,0,3,2
+            r[i] = a * r[i] + b * dpp_mov<0x4E>(r[i]);  // quad_perm 2,3,0,1
+        }
+        r[i] = a * r[i] + b * dpp_mov<0x128>(r[i]);     // row_ror 8
+    }
+    // LDS place of p1..p13, with p10 added to p3 for the banks
+    const int put0 = tid, put1 = (tid ^ 4) + (1 << 9);
+    const int get = (tid & 0x3b) | (int)(bit(2) << 2 | bit(2) << 9) | (tid >> 6) << 10;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sh[((e & 1) ? put1 : put0) + ((e >> 1) << 10)] = r[2 * e + h];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 16; ++e) r[2 * e + h] = sh[((e & 1) ? get ^ 4 : get) + ((e >> 1) << 6)];
+    }
+#pragma unroll
+    for (int j = 1; j < 5; ++j) slot(j);  // p3, p7, p8, p9
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+        if (!(i & 2)) swap_lane5(r[i], r[i | 2]);
+    slot(1);  // p6
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+        if (!(i & 4)) swap_lane4(r[i], r[i | 4]);
+    slot(2);  // p5
+    // now p1,p2,p10,p4,p7,p3 on the lanes, p11..p13 on the waves, p0,p6,p5,p8,p9 on the slots
+    const uint32_t s1 = base + spread(bit(0) << 1 | bit(1) << 2 | bit(2) << 10 | bit(3) << 4 | bit(4) << 7 |
+                                      bit(5) << 3 | (uint32_t)(tid >> 6) << 11);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const uint32_t s = s1 + spread((e & 1) << 6 | ((e >> 1) & 1) << 5 | (uint32_t)(e >> 2) << 8);
+        Pair8 v = {r[2 * e], r[2 * e + 1]};
+        if (kHigh) {
+            v.x *= half_diag(P, s, dt);
+            v.y *= half_diag(P, s + 1, dt);
+        }
+        *(Pair8*)(out + s) = v;
+    }
+}
+
 }  // namespace
 
 const char* tm_unsupported(int L) {
@@ -697,21 +805,19 @@ static TmParams tm_params(int L, double k, const int8_t* Jx, const int8_t* Jy) {
 
 static hipError_t tm_apply_params(const TmParams& P, const double* v, double* w, hipStream_t st) {
     const uint32_t n = 1u << P.N;
-    if (P.N >= kLowBits + 4) {
-        // tiles of 4096 states: 12 bits, then passes of 8 bits (rows) x 16
-        // columns, the last pass taking what is left (at least 4 bits)
-        hipError_t e = hipSuccess;
-        int bit0 = 0;
-        while (e == hipSuccess && bit0 < P.N) {
-            int nb = bit0 == 0 ? kLowBits : std::min(kMidBits, P.N - bit0);
-            if (bit0 > 0 && P.N - bit0 - nb > 0 && P.N - bit0 - nb < 4) nb = P.N - bit0 - 4;  // keep >= 4 for the last
-            const uint32_t blocks = n / 4096;
-            hipLaunchKernelGGL(k_tm_tile, dim3(blocks), dim3(256), 0, st, P, bit0 == 0 ? v : (const double*)w, w,
-                               bit0, nb, (int)(bit0 == 0), (int)(bit0 + nb == P.N));
-            e = hipGetLastError();
-            bit0 += nb;
-        }
-        return e;
+    if (P.N == kMaxN) {
+        hipLaunchKernelGGL(k_tm_half<false>, dim3(n >> 14), dim3(512), 0, st, P, v, w);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_tm_half<true>, dim3(n >> 14), dim3(512), 0, st, P, (const double*)w, w);
+        return hipGetLastError();
+    }
+    if (P.N == kLowBits + 4) {
+        hipLaunchKernelGGL(k_tm_tile, dim3(n / 4096), dim3(256), 0, st, P, v, w, 0, kLowBits, 1, 0);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_tm_tile, dim3(n / 4096), dim3(256), 0, st, P, (const double*)w, w, kLowBits, 4, 0, 1);
+        return hipGetLastError();
     }
     if (P.N > kLowBits) return hipErrorInvalidValue;  // N = L^2 is 4, 9, 16 or 25
     hipLaunchKernelGGL(k_tm_low, dim3(n >> P.N), dim3(256), 0, st, P, v, w, P.N, 1);

@@ -67,3 +67,20 @@ def test_power_iteration_over_launches():
     assert 2048 < its[0] <= 4500
     assert abs(v @ v - 1.0) <= 1e-12
     assert abs(v @ otm.apply(L, k, Jx, Jy, v) - lam[0]) <= 1e-12 * lam[0]
+
+
+def test_product_of_offset_vectors():
+    """L = 5 reads and writes pairs; vectors need only the alignment of a double."""
+    import torch
+    L, n = 5, 2 ** 25
+    Jx, Jy = _couplings(L, 8)
+    print("L = 5 product of vectors at odd places", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    a, b = (torch.empty(n + 1, dtype=torch.float64, device="cuda") for _ in range(2))
+    v = torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+    w = torch.empty_like(v)
+    tfim.tm_apply(L, 0.3, Jx, Jy, v, w)
+    a[1:].copy_(v)
+    tfim.tm_apply(L, 0.3, Jx, Jy, a[1:], b[1:])
+    torch.cuda.synchronize()
+    assert torch.equal(w, b[1:])
