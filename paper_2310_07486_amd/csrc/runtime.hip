@@ -956,6 +956,16 @@ tfim_status tfim_get_state(tfim_plan* pl, uint32_t shape, uint8_t* kidx, uint32_
     tfim_status st = shape_ok(pl, shape);
     if (st != TFIM_OK) return st;
     const ShapeHost& h = pl->shapes[shape];
+    // kidx, winv and U follow each other in the arena: a copy and its wait take
+    // some 20 us, as long as copying 256 KB again on the host
+    const size_t span = h.oU + h.nLab * 4 - h.oK;
+    if (kidx && U && span <= (256u << 10)) {
+        std::vector<uint8_t> buf(span);
+        if ((st = copy_back(pl, buf.data(), pl->arena + h.oK, span, "get state")) != TFIM_OK) return st;
+        memcpy(kidx, buf.data(), h.nLab);
+        memcpy(U, buf.data() + (h.oU - h.oK), h.nLab * 4);
+        return TFIM_OK;
+    }
     if (kidx && (st = copy_back(pl, kidx, pl->arena + h.oK, h.nLab, "get kidx")) != TFIM_OK) return st;
     if (U && (st = copy_back(pl, U, pl->arena + h.oU, h.nLab * 4, "get U")) != TFIM_OK) return st;
     return TFIM_OK;
@@ -1464,10 +1474,11 @@ tfim_status tfim_measure(tfim_plan* pl, uint32_t shape, uint32_t what, void* out
     const size_t S = samples_of(pl, h), nk = h.s.n_k, R = h.s.n_replicas;
     if (what == TFIM_MEASURE_ENERGY) {
         if (bytes < R * S * nk * 4) return fail(TFIM_EINVAL, "output buffer too small");
-        std::vector<uint8_t> winv(h.nLab);
-        std::vector<uint32_t> U(h.nLab);
-        if ((st = copy_back(pl, winv.data(), pl->arena + h.oWinv, h.nLab, "get winv")) != TFIM_OK) return st;
-        if ((st = copy_back(pl, U.data(), pl->arena + h.oU, h.nLab * 4, "get U")) != TFIM_OK) return st;
+        // one copy: winv and U follow each other in the arena, at multiples of 256
+        std::vector<uint32_t> buf((h.oU - h.oWinv) / 4 + h.nLab);
+        if ((st = copy_back(pl, buf.data(), pl->arena + h.oWinv, buf.size() * 4, "get U")) != TFIM_OK) return st;
+        const uint8_t* winv = (const uint8_t*)buf.data();
+        const uint32_t* U = buf.data() + (h.oU - h.oWinv) / 4;
         uint32_t* o = (uint32_t*)out;
         for (size_t g = 0; g < R * S; ++g)
             for (size_t i = 0; i < nk; ++i) o[g * nk + i] = U[g * nk + winv[g * nk + i]];
