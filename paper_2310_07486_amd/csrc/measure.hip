@@ -20,8 +20,8 @@
 //
 // 1. k_transpose turns the multispin words (64 samples per word) into one
 //    bit row per sample, in two layouts: bits along tau (Pt, the K axis of G)
-//    and bits along the sites (Px, the K axis of Q), by 64x64 bit transposes across
-//    a wavefront (six xor-shuffle butterfly stages).
+//    and bits along the sites (Px, the K axis of Q), by 64x64 bit transposes in the
+//    registers of a lane.
 // 2. k_gram_mfma: 64x64 tiles of G (upper triangle of tile pairs), the
 //    replicas one after the other on fp4 MFMAs and kept as int16, bucket sums
 //    in LDS; k_gram_wide (int8 MFMAs, int64 products) for Ltau > 8192.
@@ -48,16 +48,55 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 constexpr int kMaxR = 6;       // replicas handled by the MFMA kernels
 constexpr int kMaxP = kMaxR * (kMaxR - 1) / 2;
 
-constexpr int kTP = 65;  // padded row pitch (words) of the transpose tiles
-constexpr size_t kTransposeLds = (size_t)64 * kTP * 8 + 64 * 4;
+// 64 x 64 bits in the registers of a lane, row t in lo[t], hi[t]: row b becomes
+// bit b of every row.  Halves by renaming, 16 and 8 by byte permutes, then two
+// operations per dword and stage.
+__device__ __forceinline__ void lane_transpose64(uint32_t (&lo)[64], uint32_t (&hi)[64]) {
+#pragma unroll
+    for (int t = 0; t < 32; ++t) {
+        const uint32_t x = hi[t];
+        hi[t] = lo[t + 32];
+        lo[t + 32] = x;
+    }
+    auto stage = [](uint32_t (&x)[64], int j) {
+#pragma unroll
+        for (int t = 0; t < 64; ++t)
+            if (!(t & j)) {
+                const uint32_t a = x[t], b = x[t + j];
+                if (j == 16) {
+                    x[t] = __builtin_amdgcn_perm(b, a, 0x05040100);
+                    x[t + j] = __builtin_amdgcn_perm(b, a, 0x07060302);
+                } else if (j == 8) {
+                    x[t] = __builtin_amdgcn_perm(b, a, 0x06020400);
+                    x[t + j] = __builtin_amdgcn_perm(b, a, 0x07030501);
+                } else {
+                    const uint32_t m = j == 4 ? 0x0f0f0f0fu : j == 2 ? 0x33333333u : 0x55555555u;
+                    x[t] = (a & m) | ((b << j) & ~m);
+                    x[t + j] = ((a >> j) & m) | (b & ~m);
+                }
+            }
+    };
+    stage(lo, 16), stage(hi, 16);
+    stage(lo, 8), stage(hi, 8);
+    stage(lo, 4), stage(hi, 4);
+    stage(lo, 2), stage(hi, 2);
+    stage(lo, 1), stage(hi, 1);
+}
 
-__global__ void __launch_bounds__(256) k_transpose(ShapeDev sh, long long items) {
-    extern __shared__ uint64_t tlds[];
-    uint64_t(*tile)[kTP] = (uint64_t(*)[kTP])tlds;
-    int* mrow = (int*)(tlds + 64 * kTP);
+// Both layouts of the rows (Pt, Px) from the multispin words, one wave per tile
+// of 64 site slots x 64 tau.  A lane reads the 64 words of its site and
+// transposes them in registers: row b is sample b's, bits along tau, and the
+// wave's 64 lanes write it as 512 bytes of Pt.  For Px a lane needs the 64 words
+// of a tau: they change places through LDS, the low and the high dwords one
+// after the other (17 KB, eight waves per CU).  Bound by memory, of which it
+// reads the words once and writes them twice: L = 24, Ltau = 2048, 128
+// configurations of 64 lanes 1026 us (exchanges between lanes) -> 777; copy rate 750.
+constexpr int kTP = 68;  // dwords from site to site in LDS: quads of lanes on all banks
+__global__ void __launch_bounds__(64, 2) k_transpose(ShapeDev sh, long long items) {
+    __shared__ __align__(16) uint32_t swap[64 * kTP];
     const int L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, W = sh.W, R = sh.R;
     const int S = 64 * W;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lane = threadIdx.x;
     // Workgroup b runs on XCD b mod 8: an XCD takes all nx tiles of one
     // (configuration, chunk) in turn, since they share cache lines of S (a
     // tile reads 32-byte pieces of every tau plane).
@@ -69,65 +108,63 @@ __global__ void __launch_bounds__(256) k_transpose(ShapeDev sh, long long items)
         const int c = (int)(rest % sh.nc);
         const int cfg = (int)(rest / sh.nc);  // (r*nk + w)*W + j
         const int j = cfg % W, rw = cfg / W, w = rw % nk, r = rw / nk;
-        __syncthreads();
-        if (tid < 64) {
-            const int s = 64 * j + tid;
-            const int i = sh.kidx[((size_t)r * S + s) * nk + w];
-            mrow[tid] = (i * S + s) * R + r;
-        }
-        // the 64 x 64 words of the tile: all 16 loads of a thread in flight
-        // at once (the loops are unrolled so that they can be)
-        uint64_t v[16];
+        const int smp = 64 * j + lane;
+        const int mrow = (sh.kidx[((size_t)r * S + smp) * nk + w] * S + smp) * R + r;
         int x1, x2;
         slot_site(sh.L, 64 * g + lane, x1, x2);
         const bool site_ok = 64 * g + lane < L2;
-        const uint64_t* const col = sh.S + (size_t)cfg * Lt * L2 + (site_ok ? x1 + sh.L * x2 : 0);
+        const int site = site_ok ? x1 + sh.L * x2 : 0;
+        const uint64_t* const words = sh.S + ((size_t)cfg * Lt + 64 * (size_t)c) * L2;
+        const int nt = min(64, Lt - 64 * c);
+        uint32_t lo[64], hi[64];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int tau = 64 * c + wv + 4 * k;
-            v[k] = (tau < Lt && site_ok) ? col[(size_t)tau * L2] : 0ull;
+        for (int t = 0; t < 64; ++t) {
+            const uint64_t v = (words + (size_t)min(t, nt - 1) * L2)[site];
+            lo[t] = (uint32_t)v;
+            hi[t] = (uint32_t)(v >> 32);
         }
+        // padding: zero
+        if (nt < 64)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int e = tid + 256 * k;
-            tile[e >> 6][e & 63] = v[k];
+            for (int t = 1; t < 64; ++t)
+                if (t >= nt) lo[t] = hi[t] = 0;
+        if (64 * (g + 1) > L2)
+#pragma unroll
+            for (int t = 0; t < 64; ++t) {
+                lo[t] = site_ok ? lo[t] : 0;
+                hi[t] = site_ok ? hi[t] : 0;
+            }
+        uint32_t xlo[64], xhi[64];
+        auto put = [&](const uint32_t (&v)[64]) {
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < 64; t += 4)
+                *(uint4*)(swap + kTP * lane + t) = uint4{v[t], v[t + 1], v[t + 2], v[t + 3]};
+            __syncthreads();
+        };
+        auto get = [&](uint32_t (&x)[64]) {
+#pragma unroll
+            for (int u = 0; u < 64; ++u) x[u] = swap[kTP * u + lane];
+        };
+        put(lo);
+        get(xlo);
+        put(hi);
+        lane_transpose64(lo, hi);
+#pragma unroll
+        for (int b = 0; b < 64; ++b) {
+            uint64_t* const row =
+                sh.Pt + ((size_t)__builtin_amdgcn_readlane(mrow, b) * sh.nc + c) * sh.nxp + 64 * g;
+            row[lane] = (uint64_t)hi[b] << 32 | lo[b];
         }
-        __syncthreads();
-        // both transposes from the tile into registers, the sixteen of each
-        // wave independent chains of lane exchanges; then the tile's LDS
-        // serves as the staging buffer of each output in turn (one 33 KB
-        // buffer per workgroup)
-        uint64_t vt[16], vx[16];
+        get(xhi);
+        lane_transpose64(xlo, xhi);
+        if (lane < nt)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            vt[k] = tile[lane][wv * 16 + k];  // column u: lanes = tau
-            vx[k] = tile[wv * 16 + k][lane];  // row t: lanes = xy
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            vt[k] = wave_transpose64(vt[k]);  // lane = sample bit b, bits along tau
-            vx[k] = wave_transpose64(vx[k]);  // lane = sample bit b, bits along xy
-        }
-        __syncthreads();  // every wave has read the tile
-#pragma unroll
-        for (int k = 0; k < 16; ++k) tile[lane][wv * 16 + k] = vt[k];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int e = tid + 256 * k;
-            const int b = e >> 6, u = e & 63;
-            sh.Pt[((size_t)mrow[b] * sh.nc + c) * sh.nxp + 64 * g + u] = tile[b][u];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) tile[lane][wv * 16 + k] = vx[k];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int e = tid + 256 * k;
-            const int b = e >> 6, t = e & 63, tau = 64 * c + t;
-            if (tau < Lt) sh.Px[((size_t)mrow[b] * sh.nx + g) * Lt + tau] = tile[b][t];
-        }
+            for (int b = 0; b < 64; ++b) {
+                uint64_t* const row =
+                    sh.Px + ((size_t)__builtin_amdgcn_readlane(mrow, b) * sh.nx + g) * Lt + 64 * c;
+                row[lane] = (uint64_t)xhi[b] << 32 | xlo[b];
+            }
     }
 }
 
@@ -960,16 +997,10 @@ bool measure_ok(const ShapeDev& sh) { return sh.R >= 2 && sh.R <= kMaxR && sh.L 
 
 hipError_t launch_transpose(const ShapeDev& sh, hipStream_t st) {
     const long long items = (long long)sh.R * sh.nk * sh.W * sh.nc * sh.nx;
-    const int grid = (int)std::min<long long>((items + 7) / 8 * 8, 8192);
-    static bool lds_set = false;  // above 64 KiB of LDS per workgroup
-    if (!lds_set) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_transpose,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)kTransposeLds);
-        if (e != hipSuccess) return e;
-        lds_set = true;
-    }
-    hipLaunchKernelGGL(k_transpose, dim3(grid), dim3(256), kTransposeLds, st, sh, items);
+    // a multiple of 8; blocks past the last tile leave at once
+    const long long blocks = ((long long)sh.R * sh.nk * sh.W * sh.nc + 7) / 8 * 8 * sh.nx;
+    const int grid = (int)std::min<long long>(blocks, 1 << 20);
+    hipLaunchKernelGGL(k_transpose, dim3(grid), dim3(64), 0, st, sh, items);
     return hipGetLastError();
 }
 
