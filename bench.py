@@ -139,7 +139,7 @@ def measure_ops(sh):
 
 
 def measure_leg(plan, sh, torch, args):
-    """Batched int8-MFMA measurement of all configurations vs the same kernels
+    """Batched MFMA measurement of all configurations vs the same kernels
     launched per configuration and vs the plain per-sample form."""
     from paper_2310_07486_amd import tfim
     ncfg, g_ops, q_ops = measure_ops(sh)
@@ -183,15 +183,14 @@ def measure_leg(plan, sh, torch, args):
     # xi^(2) of every k from the buckets (FP64, host)
     A = plan.measure(0, tfim.TFIM_MEASURE_BUCKETS)
     xi = tfim.tfim_xi2(np.ascontiguousarray(A[:, 0]), sh.L)
-    # the Gram runs on fp4 MFMAs (peak 10.1 POP/s) where L is a multiple of 8
-    # and Ltau <= 8192, else on int8 (5 POP/s) like the overlaps
-    gram_fp4 = sh.L % 8 == 0 and sh.Ltau <= 8192
-    peak_mixed = (g_ops + q_ops) / (g_ops / (10100.0 if gram_fp4 else 5000.0) + q_ops / 5000.0)
+    # both run on fp4 MFMAs (peak 10.1 POP/s), the Gram of Ltau > 8192 on int8 (5 POP/s)
+    gram_fp4 = sh.Ltau <= 8192
+    peak_mixed = (g_ops + q_ops) / (g_ops / (10100.0 if gram_fp4 else 5000.0) + q_ops / 10100.0)
     return {
         "configurations": ncfg, "replicas": sh.n_replicas,
         "ops_per_configuration": per_cfg, "gram_ops": g_ops * ncfg, "overlap_ops": q_ops * ncfg,
-        "mfma_forms": {"gram": "fp4 (e2m1 {0, 0.5} operands, fp32 accumulate)" if gram_fp4 else "int8",
-                       "overlap": "int8"},
+        "mfma_forms": {"gram": "fp4 (e2m1 +-1 operands, fp32 accumulate)" if gram_fp4 else "int8",
+                       "overlap": "fp4 (e2m1 +-1 operands, fp32 accumulate)"},
         "transpose_ms": round(t_tr, 3),
         "batched_mfma": {"ms": round(t_all, 3), "int8_tops": round(tops, 2),
                           "frac_of_int8_peak": round(tops / 5000.0, 4),
@@ -213,16 +212,16 @@ def triples_ops(sh):
     """Integer ops of the three-replica records of one configuration.
     Algorithmic: the Gram of every replica, L^2 (L^2 + 1) Ltau, and the
     product G^f G^g of every replica pair, 2 L^6 (multiply and add counted
-    as two).  Executed on the matrix cores: the stored Gram over padded 8x8
-    site blocks (tile pairs of the upper triangle, 64 x 64 x Ltau each) and
-    four int8 products per pair over the padded Np = 64 ceil(L/8)^2 sites
-    (two digits per factor)."""
+    as two).  Executed on the matrix cores: the stored Gram on fp4 over ordered
+    pairs of 64 x 64 tiles, and four int8 products per pair over the sites
+    padded to blocks of 32 (K) and tiles of 128 (both sides; two digits per
+    factor)."""
     L2, Lt, R = sh.L * sh.L, sh.Ltau, sh.n_replicas
     P = R * (R - 1) // 2
-    nt = ((sh.L + 7) // 8) ** 2
-    Np = 64 * nt
+    nblk = ((sh.L + 3) // 4) * ((sh.L + 7) // 8)    # blocks of 4 x 8 sites
     alg = L2 * (L2 + 1) * Lt * R + 2 * L2 ** 3 * P
-    exe = (nt * (nt + 1) // 2) * 2 * 64 * 64 * (64 * ((Lt + 63) // 64)) * R + 4 * 2 * Np ** 3 * P
+    exe = (2 * (64 * ((nblk + 1) // 2)) ** 2 * (128 * ((Lt + 127) // 128)) * R
+           + 4 * 2 * (128 * ((nblk + 3) // 4)) ** 2 * (32 * nblk) * P)
     return alg, exe
 
 
@@ -248,7 +247,7 @@ def triples_leg(plan, sh, torch, args):
     tops_alg = alg * ncfg / (ms * 1e-3) / 1e12
     tops_exe = exe * ncfg / (ms * 1e-3) / 1e12
     log("bench: xi3: %d configurations in chunks of %d: %.1f ms, %.1f TOP/s algorithmic, "
-        "%.1f TOP/s int8 executed" % (ncfg, chunk, ms, tops_alg, tops_exe))
+        "%.1f TOP/s executed" % (ncfg, chunk, ms, tops_alg, tops_exe))
     rec = np.concatenate([plan.measure_triples(0, c0, min(chunk, ncfg - c0),
                                                flags=tfim.TFIM_MEASURE_REUSE_LAYOUT)
                           for c0 in range(0, ncfg, chunk)])
@@ -276,9 +275,8 @@ def timecorr_leg(plan, sh, torch, args):
     L2, Lt, R = sh.L * sh.L, sh.Ltau, sh.n_replicas
     ntt = (Lt + 63) // 64
     alg = Lt * (Lt + 1) * L2 * R                                   # symmetric H, mul + add
-    # executed: 64 x 64 tiles of the upper triangle, K = 64 per chunk plus the
-    # 32-wide correction step, replicas taken two at a time
-    exe = (ntt * (ntt + 1) // 2) * 2 * 64 * 64 * (64 * ((L2 + 63) // 64) + 32) * (2 * ((R + 1) // 2))
+    # executed: 64 x 64 tiles of the upper triangle, K = 64 per chunk
+    exe = (ntt * (ntt + 1) // 2) * 2 * 64 * 64 * (64 * ((L2 + 63) // 64)) * R
     chunk = min(args.triples_chunk, ncfg)
     stream = torch.cuda.current_stream()
     plan.measure_time(0, 0, chunk, copy=False)
@@ -295,7 +293,7 @@ def timecorr_leg(plan, sh, torch, args):
     tops_alg = alg * ncfg / (ms * 1e-3) / 1e12
     tops_exe = exe * ncfg / (ms * 1e-3) / 1e12
     log("bench: two-time: %d configurations in chunks of %d: %.1f ms, %.1f TOP/s algorithmic, "
-        "%.1f TOP/s int8 executed" % (ncfg, chunk, ms, tops_alg, tops_exe))
+        "%.1f TOP/s executed" % (ncfg, chunk, ms, tops_alg, tops_exe))
     taus = [t for t in (1, 4, 16, 64, 256, 1024) if t < Lt]
     curves = {}
     S = sh.n_samples
@@ -340,9 +338,9 @@ def transfer_leg(torch, args):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / reps
     alg = 2 * 8 * n          # read v once, write w once
-    moved = 3 * alg          # three passes over the vector
+    moved = 2 * alg          # two passes over the vector
     gbs = alg / (ms * 1e-3) / 1e9
-    log("bench: transfer: L=5 product %.3f ms, %.0f GB/s algorithmic (%.0f GB/s moved by 3 passes)"
+    log("bench: transfer: L=5 product %.3f ms, %.0f GB/s algorithmic (%.0f GB/s moved by 2 passes)"
         % (ms, gbs, moved / (ms * 1e-3) / 1e9))
     del v, w
     lam = []

@@ -183,7 +183,7 @@ tfim_status tfim_measure(tfim_plan *plan, uint32_t shape, uint32_t what, void *h
 
 /* Measurement of a range of configurations cfg = i*samples + s,
  * cfg0 .. cfg0+ncfg-1, into int64 records [ncfg][pairs][2L+3] (layout as
- * TFIM_MEASURE_RECORDS).  mode 0: batched int8-MFMA kernels (default);
+ * TFIM_MEASURE_RECORDS).  mode 0: batched MFMA kernels (default);
  * mode 1: plain per-sample form (one launch per configuration, one matrix
  * element per thread, int32 multiply-accumulate, no MFMA).  flags:
  * TFIM_MEASURE_REUSE_LAYOUT skips the bit transposition (valid only if the

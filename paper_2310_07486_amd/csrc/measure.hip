@@ -1,5 +1,4 @@
-// Measurement: replica Gram / overlap integers on int8 MFMA, fused int64
-// reductions.
+// Measurement: replica Gram / overlap integers on MFMA, fused int64 reductions.
 //
 // Paper: arXiv:2310.07486, Methods, "One-time observables" (M_xy, M-hat, the
 // susceptibilities chi^(2), F^(2) and the second-moment length) with the
@@ -41,9 +40,7 @@
 namespace tfim {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-
 
 constexpr int kMaxR = 6;       // replicas handled by the MFMA kernels
 constexpr int kMaxP = kMaxR * (kMaxR - 1) / 2;

@@ -61,7 +61,9 @@ struct tfim_plan {
     // failure injection (TFIM_FAIL_AFTER): the n-th enqueueing call fails
     int64_t fail_after = 0;
     std::vector<uint64_t> t, m;  // host mirrors per shape
-    bool counters_behind = false;  // the device's counters are older than the mirrors
+    // per-shape kernels read the device's counters: a call was captured in the
+    // caller's own graph, whose replays go on from where the last one ended
+    bool device_counters = false;
     uint32_t schedule = TFIM_SCHED_PER_SHAPE;
     int variant = 3;  // helper waves where L = 24, else the streaming kernel
     uint32_t measure_mode = 0;
@@ -585,20 +587,42 @@ static hipError_t timed_sweep(tfim_plan* pl, int i, bool energy) {
     std::pair<hipEvent_t, hipEvent_t> ev;
     hipError_t e = timing_begin(pl, ev);
     if (e == hipSuccess)
-        e = tfim::launch_sweep(dev_of(pl, i), pl->seed, tfim::When{(uint32_t)pl->t[i], nullptr}, pl->variant, energy,
-                               pl->n_cu, pl->stream);
+        e = tfim::launch_sweep(dev_of(pl, i), pl->seed,
+                               tfim::When{(uint32_t)pl->t[i], pl->device_counters ? counters_of(pl, i) : nullptr},
+                               pl->variant, energy, pl->n_cu, pl->stream);
     return timing_end(pl, ev, 1, e);
 }
 
 static hipError_t temper(tfim_plan* pl, int i) {
     if (plain(pl)) return tfim::plain_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i], pl->stream);
-    return tfim::launch_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i], pl->stream);
+    return tfim::launch_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i],
+                               pl->device_counters ? counters_of(pl, i) : nullptr, pl->stream);
+}
+
+// Before per-shape launches: is this call being captured?
+static void watch_capture(tfim_plan* pl) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(pl->stream, &s) != hipSuccess) (void)hipGetLastError();
+    else if (s == hipStreamCaptureStatusActive) pl->device_counters = true;
+}
+
+// After a call whose launches took the counters by value: the device's own, which
+// graphs read (the other schedules', or the caller's if it captures the next call).
+static hipError_t set_device_counters(tfim_plan* pl) {
+    if (pl->device_counters) return hipSuccess;
+    tfim::CounterValues v{};
+    for (size_t i = 0; i < pl->shapes.size(); ++i) {
+        v.t[i] = (uint32_t)pl->t[i];
+        v.m[i] = (uint32_t)pl->m[i];
+    }
+    return tfim::launch_set_counters(counters_of(pl, 0), v, (int)pl->shapes.size(), pl->stream);
 }
 
 // Enqueue one sweep of every shape (plus due tempering) with the per-shape
 // schedule; the host mirrors pl->t, pl->m hold each shape's counters and go to
-// the kernels by value (the device's own counters serve the graphs of the other
-// schedules and are brought up to date before those).  U is recounted when a tempering step follows or when the caller will see it.
+// the kernels by value, which saves a launch per sweep; captured calls and those
+// after them advance the device's.  U is recounted when a tempering step follows
+// or when the caller will see it.
 static hipError_t enqueue_sweep(tfim_plan* pl, bool last) {
     hipError_t e = hipSuccess;
     const int ns = (int)pl->shapes.size();
@@ -611,8 +635,9 @@ static hipError_t enqueue_sweep(tfim_plan* pl, bool last) {
         const uint32_t pe = pl->shapes[i].s.pt_every;
         const bool due = pe > 0 && ((pl->t[i] + 1) % pe) == 0;
         if (due) e = temper(pl, i);
+        if (e == hipSuccess && pl->device_counters)
+            e = tfim::launch_advance(counters_of(pl, i), 1u, due ? 1u : 0u, pl->stream);
     }
-    pl->counters_behind = true;
     return e;
 }
 
@@ -639,7 +664,6 @@ static hipError_t enqueue_plain(tfim_plan* pl, uint64_t n) {
             }
         }
     }
-    pl->counters_behind = true;
     return e;
 }
 
@@ -850,16 +874,6 @@ static hipError_t batch_graph(tfim_plan* pl, uint32_t g, hipGraphExec_t* out) {
 
 static hipError_t enqueue_batched(tfim_plan* pl, uint64_t n) {
     hipError_t e = hipSuccess;
-    if (pl->counters_behind) {
-        tfim::CounterValues v{};
-        for (size_t i = 0; i < pl->shapes.size(); ++i) {
-            v.t[i] = (uint32_t)pl->t[i];
-            v.m[i] = (uint32_t)pl->m[i];
-        }
-        e = tfim::launch_set_counters(counters_of(pl, 0), v, (int)pl->shapes.size(), pl->stream);
-        if (e != hipSuccess) return e;
-        pl->counters_behind = false;
-    }
     while (n > 0 && e == hipSuccess) {
         const uint32_t g = (uint32_t)std::min<uint64_t>(n, kGraphSweeps);
         hipGraphExec_t ex = nullptr;
@@ -898,10 +912,12 @@ static tfim_status sweep_impl(tfim_plan* pl, uint64_t n) {
     } else if (plain(pl)) {
         e = enqueue_plain(pl, n);
     } else {
+        watch_capture(pl);
         for (uint64_t s = 0; s < n && e == hipSuccess; ++s) {
             e = enqueue_sweep(pl, s + 1 == n);  // reads the mirrors of this sweep
             if (e == hipSuccess) advance(1);
         }
+        if (e == hipSuccess) e = set_device_counters(pl);
     }
     return check_hip(pl, e, "sweep");
 }
@@ -916,11 +932,14 @@ tfim_status tfim_pt_swap(tfim_plan* pl) {
         if (pl->m[i] >= 0xFFFFFFFFull) return fail(TFIM_EOVERFLOW, "tempering counter overflow");
     if ((st = injected(pl)) != TFIM_OK) return st;
     hipError_t e = hipSuccess;
+    watch_capture(pl);
     for (size_t i = 0; i < pl->shapes.size() && e == hipSuccess; ++i) {
         e = temper(pl, (int)i);
+        if (e == hipSuccess && pl->device_counters)
+            e = tfim::launch_advance(counters_of(pl, (int)i), 0u, 1u, pl->stream);
         pl->m[i] += 1;
     }
-    pl->counters_behind = true;
+    if (e == hipSuccess && !plain(pl)) e = set_device_counters(pl);
     return check_hip(pl, e, "pt_swap");
 }
 

@@ -128,9 +128,9 @@ __device__ void temper_group(const ShapeDev& sh, int r, int j, uint32_t key0, ui
 }
 
 __global__ void __launch_bounds__(kTemperThreads) k_temper(ShapeDev sh, uint32_t key0, uint32_t key1,
-                                               uint32_t m) {
+                                               uint32_t m, const Counters* ctr) {
     extern __shared__ uint8_t kl[];  // [64][nk] labels, then [64][nk] inverse
-    temper_group(sh, (int)blockIdx.x / sh.W, (int)blockIdx.x % sh.W, key0, key1, m, kl);
+    temper_group(sh, (int)blockIdx.x / sh.W, (int)blockIdx.x % sh.W, key0, key1, ctr ? ctr->m : m, kl);
 }
 
 __device__ __forceinline__ bool pt_due(const ShapeDev& sh, uint32_t t) {
@@ -157,6 +157,13 @@ __global__ void k_advance_batch(TemperBatchArgs a) {
         const bool due = pt_due(a.shapes[s], t);
         a.ctr[s].t = t + 1;
         a.ctr[s].m += due ? 1u : 0u;
+    }
+}
+
+__global__ void k_advance(Counters* ctr, uint32_t dt, uint32_t dm) {
+    if (threadIdx.x == 0) {
+        ctr->t += dt;
+        ctr->m += dm;
     }
 }
 
@@ -202,9 +209,14 @@ hipError_t launch_mask_rebuild(const ShapeDev& sh, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st) {
+hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, const Counters* ctr, hipStream_t st) {
     hipLaunchKernelGGL(k_temper, dim3(sh.R * sh.W), dim3(kTemperThreads), (size_t)128 * sh.nk, st, sh,
-                       (uint32_t)seed, (uint32_t)(seed >> 32), m);
+                       (uint32_t)seed, (uint32_t)(seed >> 32), m, ctr);
+    return hipGetLastError();
+}
+
+hipError_t launch_advance(Counters* ctr, uint32_t dt, uint32_t dm, hipStream_t st) {
+    hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, st, ctr, dt, dm);
     return hipGetLastError();
 }
 

@@ -163,21 +163,9 @@ __device__ __forceinline__ i32x4 mfma_bits_operand(uint32_t x) {
     return o;
 }
 
-// v_mfma_scale_f32_32x32x64_f8f6f4 operands: format code 4 = e2m1 (fp4) on
-// both sides, four registers of 8 nibbles each; block scales are E8M0
-// (2^(e - 127)): 2^4 on the row side, 1 on the column side
+// v_mfma_f32_32x32x64_f8f6f4 operands: format code 4 = e2m1 (fp4) on both
+// sides, four registers of 8 nibbles each
 constexpr int kFp4 = 4;
-constexpr int kScaleRow = 127 + 4;
-constexpr int kScaleOne = 127;
-// Bit 4j + m of x (m < 4, j < 8) as the fp4 nibble j of register m: 0 or
-// 0.5; the upper four registers are not read in the fp4 form.
-__device__ __forceinline__ i32x8 fp4_bits_operand(uint32_t x) {
-    i32x4 o;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) o[m] = (int)((x >> m) & 0x11111111u);
-    return __builtin_shufflevector(o, o, 0, 1, 2, 3, -1, -1, -1, -1);
-}
-
 // Bit 4j + m of x (m < 4, j < 8) as the fp4 nibble j of register m: -1 where
 // the bit is set, else +1 (mag = 0x22222222: e2m1 1.0 is 0010, the bit goes to
 // the sign), or +-0 (mag = 0).  mag sits in a vector register, so that each
@@ -209,18 +197,6 @@ __host__ __device__ inline void slot_site(int L, int slot, int& x1, int& x2) {
     const int a = slot / (4 * L), rem = slot - 4 * L * a, two = L - 4 * a < 4;
     x2 = two ? rem >> 1 : rem >> 2;
     x1 = 4 * a + (two ? rem & 1 : rem & 3);
-}
-
-// Sixteen int8 bytes summing to v, |v| <= 1792: fifteen of floor(v / 16) and
-// one of floor(v / 16) + (v mod 16).  Against sixteen ones on the other side
-// of one K step it adds v to every element of a row (or column).
-__device__ __forceinline__ i32x4 mfma_pieces16(int v) {
-    const int q = v >> 4, r = v & 15;
-    const uint32_t rep = (uint32_t)(q & 0xFF) * 0x01010101u;
-    i32x4 o;
-    o[0] = (int)((rep & 0xFFFFFF00u) | (uint32_t)((q + r) & 0xFF));
-    o[1] = o[2] = o[3] = (int)rep;
-    return o;
 }
 
 }  // namespace tfim
@@ -272,14 +248,16 @@ hipError_t launch_sweep_batch(const BatchArgs& a, int occ, bool anti, int blocks
 // counter advance t += 1, m += due.
 hipError_t launch_temper_batch(const TemperBatchArgs& a, int blocks, int max_nk, hipStream_t st);
 hipError_t launch_advance_batch(const TemperBatchArgs& a, hipStream_t st);
-hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st);
+// m by value, or (ctr not null) the device's
+hipError_t launch_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, const Counters* ctr, hipStream_t st);
+hipError_t launch_advance(Counters* ctr, uint32_t dt, uint32_t dm, hipStream_t st);
 // Counters of the first n <= 64 shapes set to the given values.
 struct CounterValues {
     uint32_t t[64], m[64];
 };
 hipError_t launch_set_counters(Counters* ctr, const CounterValues& v, int n, hipStream_t st);
 // Measurement of configurations cfg0 .. cfg0+ncfg-1 (cfg = i*S + s) into the
-// records (which must be zeroed first).  mode 0: batched int8-MFMA kernels;
+// records (which must be zeroed first).  mode 0: batched MFMA kernels;
 // mode 1: plain per-sample VALU form, one launch per configuration.
 hipError_t launch_transpose(const ShapeDev& sh, hipStream_t st);
 hipError_t launch_measure(const ShapeDev& sh, int mode, int cfg0, int ncfg, hipStream_t st);

@@ -66,3 +66,37 @@ def test_counters_across_schedules():
         got.append(_state(plan))
         plan.close()
     assert _same(*got)
+
+
+def test_callers_graph_goes_on():
+    """tfim_sweep and tfim_pt_swap captured in the caller's own graph: every
+    replay does the next sweeps, eager calls before and after go on likewise."""
+    import torch
+    shapes = [Shape(4, 32, 1, 2, ladder(0.2, 0.4, 3), pt_every=1),
+              Shape(6, 40, 1, 2, ladder(0.2, 0.4, 2), pt_every=2, stream_id=1)]
+    print("caller's graph", flush=True)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        plan, ref = tfim.Plan(shapes, 5, stream=st), tfim.Plan(shapes, 5, stream=st)
+        for p in (plan, ref):
+            p.init()
+            p.sweep(2)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            plan.sweep(4)
+            plan.pt_swap()
+        for k in range(3):
+            g.replay()
+            ref.sweep(4)
+            ref.pt_swap()
+            torch.cuda.synchronize()
+            for i in range(2):
+                assert np.array_equal(plan.export_spins(i), ref.export_spins(i)), (k, i)
+                assert all(np.array_equal(a, b) for a, b in zip(plan.get_state(i), ref.get_state(i))), (k, i)
+        plan.sweep(4)
+        ref.sweep(4)
+        for i in range(2):
+            assert np.array_equal(plan.export_spins(i), ref.export_spins(i))
+        plan.close()
+        ref.close()
