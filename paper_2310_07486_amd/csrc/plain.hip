@@ -69,7 +69,8 @@ __global__ void k_plain_init_spins(ShapeDev sh, uint32_t key0, uint32_t key1) {
 // R < Tu[k-index][u] with u = (12 - dE)/4 unsatisfied bonds.  Sites of one
 // colour only neighbour the other colour, so threads never race.
 __global__ void __launch_bounds__(256) k_plain_half(ShapeDev sh, uint32_t key0, uint32_t key1,
-                                                    uint32_t t, int c) {
+                                                    When when, uint32_t ahead, int c) {
+    const uint32_t t = when.get() + ahead;
     int8_t* S8 = (int8_t*)sh.S;
     const int8_t* J = (const int8_t*)sh.J;
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W;
@@ -140,7 +141,7 @@ __host__ __device__ inline size_t plain_run_lds(const ShapeDev& sh) {
 
 template <bool kOne>
 __global__ void __launch_bounds__(kPlainRunThreads)
-k_plain_run(ShapeDev sh, uint32_t key0, uint32_t key1, uint32_t t0, uint32_t n) {
+k_plain_run(ShapeDev sh, uint32_t key0, uint32_t key1, When when, uint32_t n, Counters* ctr) {
     extern __shared__ __align__(16) char lds[];  // [L2] columns, [Ltau][L2] spins
     __shared__ uint32_t tot;
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W;
@@ -160,6 +161,7 @@ k_plain_run(ShapeDev sh, uint32_t key0, uint32_t key1, uint32_t t0, uint32_t n) 
                           J[xm],        J[e],         J[L2 + ym],   J[L2 + e], (x + y) & 1};
     }
     if (tid == 0) tot = 0;
+    const uint32_t t0 = when.get();
     const uint32_t* const Tu = sh.Tu + 3 * sh.kidx[((size_t)r * ns + s) * nk + w];
     const uint32_t T0 = Tu[0], T1 = Tu[1], T2 = Tu[2];
     const uint32_t c3 = ctr_word3(plain_word(sh, s), sh.sid, kTagMetro);
@@ -208,12 +210,14 @@ k_plain_run(ShapeDev sh, uint32_t key0, uint32_t key1, uint32_t t0, uint32_t n) 
     for (int e = tid; e < L2 * Lt / 4; e += nthr) cf[e] = ((const int*)sp)[e];
     __syncthreads();
     if (tid == 0) sh.U[((size_t)r * ns + s) * nk + w] = tot;
+    if (ctr && cfg == 0 && tid == 0) ctr->t = t0 + n;
 }
 
 // Unsatisfied bonds U of every configuration from the action: each site
 // counts its +x, +y and +tau bonds (E = 2U - 3N).  One workgroup per
-// configuration.
-__global__ void __launch_bounds__(1024) k_plain_energy(ShapeDev sh) {
+// configuration.  After half-sweeps that took t by value it leaves the sweep
+// counter they reached on the device.
+__global__ void __launch_bounds__(1024) k_plain_energy(ShapeDev sh, Counters* ctr, uint32_t t) {
     __shared__ uint32_t tot;
     const int8_t* S8 = (const int8_t*)sh.S;
     const int8_t* J = (const int8_t*)sh.J;
@@ -241,15 +245,19 @@ __global__ void __launch_bounds__(1024) k_plain_energy(ShapeDev sh) {
     atomicAdd(&tot, u);
     __syncthreads();
     if (threadIdx.x == 0) sh.U[((size_t)r * ns + s) * nk + w] = tot;
+    if (ctr && cfg == 0 && threadIdx.x == 0) ctr->t = t;
 }
 
 // One tempering step for every (r, s): pairs (i, i+1), i = m mod 2, m mod 2 + 2,
 // ...; d = U_a - U_b of the walkers at k_i, k_{i+1}; accept iff d <= 0 or
 // R < Tpt[i][d] (the exchange ratio with E = 2U - 3N); R = output s%4 of the
 // Philox call ((s%64)/4 | i << 4, m, r, word j), one uniform per sample.
-__global__ void k_plain_temper(ShapeDev sh, uint32_t key0, uint32_t key1, uint32_t m) {
+__global__ void k_plain_temper(ShapeDev sh, uint32_t key0, uint32_t key1, uint32_t m_value, const Counters* read,
+                               Counters* ctr) {
+    const uint32_t m = read ? read->m : m_value;
     const int nk = sh.nk, ns = sh.W;
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (ctr && g == 0) ctr->m = m + 1;
     if (g >= sh.R * ns) return;
     const int r = g / ns, s = g % ns;
     const uint32_t b = (uint32_t)(s & 63);
@@ -442,12 +450,15 @@ hipError_t plain_labels_identity(const ShapeDev& sh, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t plain_energy(const ShapeDev& sh, hipStream_t st) {
-    hipLaunchKernelGGL(k_plain_energy, dim3(sh.R * sh.nk * sh.W), dim3(std::min(1024, (sh.L2 * sh.Lt + 63) / 64 * 64)), 0, st, sh);
+static hipError_t energy_and_counter(const ShapeDev& sh, Counters* ctr, uint32_t t, hipStream_t st) {
+    hipLaunchKernelGGL(k_plain_energy, dim3(sh.R * sh.nk * sh.W), dim3(std::min(1024, (sh.L2 * sh.Lt + 63) / 64 * 64)), 0, st, sh, ctr, t);
     return hipGetLastError();
 }
 
-hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, hipStream_t st) {
+hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, Counters* ctr, bool from_device,
+                        hipStream_t st) {
+    const When when{t, from_device ? ctr : nullptr};
+    Counters* const store = from_device ? nullptr : ctr;
     const size_t total = (size_t)sh.R * sh.nk * sh.W * sh.L2 * ((sh.Lt + 7) / 8);
     const int units = sh.L2 * ((sh.Lt + 7) / 8), ncfg = sh.R * sh.nk * sh.W;
     // A workgroup per configuration, unless a run of several sweeps goes over
@@ -458,24 +469,30 @@ hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t 
     if (plain_run_lds(sh) <= kPlainLds && (units <= 4 * kPlainRunThreads || ncfg > 8 || n == 1)) {
         const int threads = std::min(kPlainRunThreads, (units + 63) / 64 * 64);
         hipLaunchKernelGGL(units <= threads ? k_plain_run<true> : k_plain_run<false>, dim3(sh.R * sh.nk * sh.W),
-                           dim3(threads), plain_run_lds(sh), st, sh, (uint32_t)seed, (uint32_t)(seed >> 32), t, n);
-        return hipGetLastError();
+                           dim3(threads), plain_run_lds(sh), st, sh, (uint32_t)seed, (uint32_t)(seed >> 32), when, n, store);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess && from_device ? launch_advance(ctr, n, 0, st) : e;
     }
     for (uint32_t k = 0; k < n; ++k)
         for (int c = 0; c < 2; ++c) {
             hipLaunchKernelGGL(k_plain_half, dim3(grid_of(total)), dim3(256), 0, st, sh, (uint32_t)seed,
-                               (uint32_t)(seed >> 32), t + k, c);
+                               (uint32_t)(seed >> 32), when, k, c);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-    return plain_energy(sh, st);
+    const hipError_t e = energy_and_counter(sh, store, t + n, st);
+    return e == hipSuccess && from_device ? launch_advance(ctr, n, 0, st) : e;
 }
 
-hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st) {
+hipError_t plain_energy(const ShapeDev& sh, hipStream_t st) { return energy_and_counter(sh, nullptr, 0, st); }
+
+hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, Counters* ctr, bool from_device,
+                        hipStream_t st) {
     const int n = sh.R * sh.W;
     hipLaunchKernelGGL(k_plain_temper, dim3((n + 63) / 64), dim3(64), 0, st, sh, (uint32_t)seed,
-                       (uint32_t)(seed >> 32), m);
-    return hipGetLastError();
+                       (uint32_t)(seed >> 32), m, from_device ? ctr : nullptr, from_device ? nullptr : ctr);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess && from_device ? launch_advance(ctr, 0, 1, st) : e;
 }
 
 bool plain_measure_ok(const ShapeDev& sh) { return sh.R >= 2 && sh.R <= 6 && sh.L <= 24; }

@@ -594,7 +594,9 @@ static hipError_t timed_sweep(tfim_plan* pl, int i, bool energy) {
 }
 
 static hipError_t temper(tfim_plan* pl, int i) {
-    if (plain(pl)) return tfim::plain_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i], pl->stream);
+    if (plain(pl))
+        return tfim::plain_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i], counters_of(pl, i),
+                                  pl->device_counters, pl->stream);
     return tfim::launch_temper(dev_of(pl, i), pl->seed, (uint32_t)pl->m[i],
                                pl->device_counters ? counters_of(pl, i) : nullptr, pl->stream);
 }
@@ -608,6 +610,7 @@ static void watch_capture(tfim_plan* pl) {
 
 // After a call whose launches took the counters by value: the device's own, which
 // graphs read (the other schedules', or the caller's if it captures the next call).
+// The plain form's kernels leave theirs by themselves.
 static hipError_t set_device_counters(tfim_plan* pl) {
     if (pl->device_counters) return hipSuccess;
     tfim::CounterValues v{};
@@ -654,7 +657,8 @@ static hipError_t enqueue_plain(tfim_plan* pl, uint64_t n) {
             std::pair<hipEvent_t, hipEvent_t> ev;
             e = timing_begin(pl, ev);
             if (e == hipSuccess)
-                e = tfim::plain_sweeps(dev_of(pl, (int)i), pl->seed, (uint32_t)pl->t[i], (uint32_t)run, pl->stream);
+                e = tfim::plain_sweeps(dev_of(pl, (int)i), pl->seed, (uint32_t)pl->t[i], (uint32_t)run,
+                                       counters_of(pl, (int)i), pl->device_counters, pl->stream);
             e = timing_end(pl, ev, (uint32_t)run, e);
             if (e != hipSuccess) break;
             pl->t[i] += run;
@@ -910,6 +914,7 @@ static tfim_status sweep_impl(tfim_plan* pl, uint64_t n) {
         e = enqueue_batched(pl, n);
         if (e == hipSuccess) advance(n);
     } else if (plain(pl)) {
+        watch_capture(pl);
         e = enqueue_plain(pl, n);
     } else {
         watch_capture(pl);
@@ -935,7 +940,7 @@ tfim_status tfim_pt_swap(tfim_plan* pl) {
     watch_capture(pl);
     for (size_t i = 0; i < pl->shapes.size() && e == hipSuccess; ++i) {
         e = temper(pl, (int)i);
-        if (e == hipSuccess && pl->device_counters)
+        if (e == hipSuccess && pl->device_counters && !plain(pl))
             e = tfim::launch_advance(counters_of(pl, (int)i), 0u, 1u, pl->stream);
         pl->m[i] += 1;
     }

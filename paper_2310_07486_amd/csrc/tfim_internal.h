@@ -302,9 +302,13 @@ hipError_t plain_init_couplings(const ShapeDev& sh, uint64_t seed, hipStream_t s
 hipError_t plain_init_spins(const ShapeDev& sh, uint64_t seed, hipStream_t st);
 hipError_t plain_labels_identity(const ShapeDev& sh, hipStream_t st);
 hipError_t plain_energy(const ShapeDev& sh, hipStream_t st);
-// n >= 1 sweeps t, t + 1, .. and the energy recount after the last
-hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, hipStream_t st);
-hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, hipStream_t st);
+// n >= 1 sweeps t, t + 1, .. and the energy recount after the last; one tempering
+// step m.  from_device: t, m are read from ctr and ctr is advanced by a launch of
+// its own; else they go by value and the last kernel stores what follows in ctr.
+hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, Counters* ctr, bool from_device,
+                        hipStream_t st);
+hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, Counters* ctr, bool from_device,
+                        hipStream_t st);
 bool plain_measure_ok(const ShapeDev& sh);
 // pair records of configurations cfg0 .. cfg0+ncfg-1 (zeroed first)
 hipError_t plain_measure(const ShapeDev& sh, int cfg0, int ncfg, hipStream_t st);

@@ -38,3 +38,45 @@ def test_runs_of_sweeps(L, Lt, ns, nk, pt, bc):
     assert plan.counters() == (7, 7 // pt if pt else 0)
     assert np.array_equal(plan.measure(0, tfim.TFIM_MEASURE_RECORDS), om.measure_chain(ch))
     plan.close()
+
+
+@pytest.mark.parametrize("L,Lt,ns,nk,pt", [
+    (6, 30, 2, 3, 1),        # LDS, tempering after every sweep
+    (8, 32, 2, 2, 0),        # LDS, one run, tempering by tfim_pt_swap alone
+    (16, 238, 1, 2, 2),      # half-sweep launches
+])
+def test_callers_graph_goes_on(L, Lt, ns, nk, pt):
+    """tfim_sweep and tfim_pt_swap captured in the caller's own graph: every
+    replay does the next sweeps, eager calls before and after go on likewise."""
+    import torch
+    shapes = [Shape(L, Lt, ns, 2, ladder(0.22, 0.3, nk), pt_every=pt, stream_id=3),
+              Shape(4, 16, 1, 2, ladder(0.2, 0.4, 3), pt_every=2, stream_id=1)]
+    _say(f"plain caller's graph L={L} Lt={Lt} samples={ns} nk={nk} pt={pt}")
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        plan, ref = (tfim.Plan(shapes, 5, stream=st, form=PLAIN) for _ in range(2))
+        for p in (plan, ref):
+            p.init()
+            p.sweep(2)
+            p.pt_swap()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            plan.sweep(4)
+            plan.pt_swap()
+        for k in range(3):
+            g.replay()
+            ref.sweep(4)
+            ref.pt_swap()
+            torch.cuda.synchronize()
+            for i in range(2):
+                assert np.array_equal(plan.export_spins(i), ref.export_spins(i)), (k, i)
+                assert all(np.array_equal(a, b) for a, b in zip(plan.get_state(i), ref.get_state(i))), (k, i)
+        for p in (plan, ref):
+            p.sweep(3)
+            p.pt_swap()
+        for i in range(2):
+            assert np.array_equal(plan.export_spins(i), ref.export_spins(i))
+            assert all(np.array_equal(a, b) for a, b in zip(plan.get_state(i), ref.get_state(i)))
+        plan.close()
+        ref.close()
