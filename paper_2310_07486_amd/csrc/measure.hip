@@ -899,13 +899,14 @@ hipError_t launch_overlap_nx(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hi
     const int npanel = (sh.Lt + 32 * NU - 1) / (32 * NU), ntt = (sh.Lt + 63) / 64;
     int nsplit = 1;
     while ((long long)ncfg * npanel * nsplit < 2 * ncu && kOverlapWaves * nsplit < ntt) nsplit *= 2;
-    const bool grouped = ncu % 8 == 0 && ncfg >= 128;
-    const long long items = (long long)ncfg * npanel * nsplit;
-    const long long grid = grouped ? (long long)((ncfg + 7) / 8) * 8 * npanel * nsplit : items;
-    hipLaunchKernelGGL((k_overlap_mfma<NU, NX>), dim3((unsigned)grid), dim3(64 * kOverlapWaves),
-                       (size_t)sh.nx * NU * 64 * 16 + (size_t)64 * sh.P * 12, st, sh,
-                       cfg0, ncfg, npanel, nsplit, (int)grouped);
-    return hipGetLastError();
+    const long long per = (long long)npanel * nsplit;
+    return over_ranges(ncfg, per, 64 * kOverlapWaves, [&](int c, int n) {
+        const bool grouped = ncu % 8 == 0 && n >= 128;
+        hipLaunchKernelGGL((k_overlap_mfma<NU, NX>), dim3((unsigned)((grouped ? (n + 7) / 8 * 8 : n) * per)),
+                           dim3(64 * kOverlapWaves), (size_t)sh.nx * NU * 64 * 16 + (size_t)64 * sh.P * 12, st, sh,
+                           cfg0 + c, n, npanel, nsplit, (int)grouped);
+        return hipGetLastError();
+    });
 }
 
 template <int NU>
@@ -929,13 +930,11 @@ hipError_t launch_gram(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStrea
     const int nblk = gram_nblk(sh.L), ntile = (nblk + 1) / 2, ntp = ntile * (ntile + 1) / 2;
     int ncw = ntp == 1 ? 4 : (ntp <= 10 ? 2 : 1);
     while (ncw > 1 && (ncfg + ncw - 1) / ncw < 2 * ncu) ncw /= 2;
-    const int nitem = (ncfg + ncw - 1) / ncw;
-    const bool grouped = ncu % 8 == 0 && nitem >= 128;
     // from 36 tiles (L >= 18) three workgroups share a configuration: the
     // rows are read by as many fewer configurations at a time through an
     // L2 (L = 24: 907 -> 876 us; L = 12 with its 6 tiles 172 -> 198)
     int nsplit = ntp >= 36 ? 3 : 1;
-    while (nitem * nsplit < 2 * ncu && kGramWaves * nsplit < ncw * ntp) nsplit *= 2;
+    while ((ncfg + ncw - 1) / ncw * (long long)nsplit < 2 * ncu && kGramWaves * nsplit < ncw * ntp) nsplit *= 2;
     // copies of the buckets: 8, or 4 where 8 would not leave room for two
     // workgroups on a CU
     const size_t one = (size_t)ncw * 4 * sh.L * gram_pitch(PP) * 8;
@@ -947,9 +946,13 @@ hipError_t launch_gram(const ShapeDev& sh, int cfg0, int ncfg, int ncu, hipStrea
         if (e != hipSuccess) return e;
         lds_set = true;
     }
-    hipLaunchKernelGGL(k_gram_mfma<RR>, dim3((unsigned)((grouped ? (nitem + 7) / 8 * 8 : nitem) * nsplit)),
-                       dim3(64 * kGramWaves), ncopy * one, st, sh, cfg0, ncfg, ncw, nsplit, ncopy, (int)grouped);
-    return hipGetLastError();
+    return over_ranges(ncfg, nsplit, 64 * kGramWaves, [&](int c, int n) {
+        const int nitem = (n + ncw - 1) / ncw;
+        const bool grouped = ncu % 8 == 0 && nitem >= 128;
+        hipLaunchKernelGGL(k_gram_mfma<RR>, dim3((unsigned)(grouped ? (nitem + 7) / 8 * 8 : nitem) * nsplit),
+                           dim3(64 * kGramWaves), ncopy * one, st, sh, cfg0 + c, n, ncw, nsplit, ncopy, (int)grouped);
+        return hipGetLastError();
+    });
 }
 
 template <int RR>

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace tfim {
 
 // Philox4x32-10 purposes (fourth counter word, bits 28..31).
@@ -197,6 +199,20 @@ __host__ __device__ inline void slot_site(int L, int slot, int& x1, int& x2) {
     const int a = slot / (4 * L), rem = slot - 4 * L * a, two = L - 4 * a < 4;
     x2 = two ? rem >> 1 : rem >> 2;
     x1 = 4 * a + (two ? rem & 1 : rem & 3);
+}
+
+// A launch may hold fewer than 2^32 work-items along x.  f(c, n) for ranges of
+// configurations c .. c + n - 1 that keep below that, `blocks` workgroups of
+// `threads` to a configuration (one range unless there are millions of them); every
+// range but the last is a multiple of 64 configurations.
+template <class F>
+hipError_t over_ranges(int ncfg, long long blocks, int threads, F f) {
+    const long long most = std::max(64ll, (0xFFFFFFFFll / threads / blocks) & ~63ll);
+    for (long long c = 0; c < ncfg; c += most) {
+        const hipError_t e = f((int)c, (int)std::min(most, ncfg - c));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace tfim

@@ -1,0 +1,32 @@
+"""More configurations than one launch can hold (2^32 work-items): the call
+goes over them in ranges.  The first and the last samples, the border between
+two ranges among them, equal those of a small plan whose words are the same
+ones of the random streams."""
+import numpy as np
+import pytest
+
+from paper_2310_07486_amd import tfim
+from paper_2310_07486_amd.workloads import Shape
+
+pytestmark = pytest.mark.gpu
+
+WORDS = 1 << 18  # 2^24 samples
+
+
+def _plan(W, offset):
+    plan = tfim.Plan([Shape(2, 16, W, 2, [0.3], word_offset=offset)], 12)
+    plan.init()
+    plan.sweep(2)
+    return plan
+
+
+def test_pair_records():
+    print("pair records of 2^24 configurations", flush=True)
+    plan = _plan(WORDS, 0)
+    rec = plan.measure_range(0, 0, 0, 64 * WORDS)
+    plan.close()
+    assert np.array_equal(rec[..., :2].sum(axis=-1), rec[..., 5])  # sum_d D_x[d] = sum Q^2
+    for offset, part in ((0, rec[:256]), (WORDS - 4, rec[-256:])):
+        small = _plan(4, offset)
+        assert np.array_equal(part, small.measure_range(0, 0, 0, 256)), offset
+        small.close()
