@@ -230,8 +230,7 @@ hipError_t launch_timecorr_as(const ShapeDev& sh, int cfg0, int ncfg, int64_t* r
     // the workgroups); more where there are few configurations.
     const int ntt = (sh.Lt + 63) / 64, ntp = ntt * (ntt + 1) / 2;
     int nsplit = std::max(1, std::min(4, ntp / (32 * kTcWaves)));
-    while (ncfg * nsplit < 2 * ncu && kTcWaves * nsplit < ntp) nsplit *= 2;
-    const bool grouped = ncu % 8 == 0 && ncfg >= 128;
+    while ((long long)ncfg * nsplit < 2 * ncu && kTcWaves * nsplit < ntp) nsplit *= 2;
     if (nsplit > 1) {
         const size_t n = (size_t)ncfg * 2 * sh.Lt;
         hipLaunchKernelGGL(k_zero_time, dim3((unsigned)std::min<size_t>((n + 255) / 256, 1024)), dim3(256), 0, st, rec,
@@ -239,9 +238,13 @@ hipError_t launch_timecorr_as(const ShapeDev& sh, int cfg0, int ncfg, int64_t* r
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_timecorr_mfma<kOdd, kWide>), dim3((unsigned)((grouped ? (ncfg + 7) / 8 * 8 : ncfg) * nsplit)),
-                       dim3(64 * kTcWaves), lds(sh.Lt), st, sh, cfg0, ncfg, nsplit, (int)grouped, rec);
-    return hipGetLastError();
+    return over_ranges(ncfg, nsplit, 64 * kTcWaves, [&](int c, int n) {
+        const bool grouped = ncu % 8 == 0 && n >= 128;
+        hipLaunchKernelGGL((k_timecorr_mfma<kOdd, kWide>), dim3((unsigned)(grouped ? (n + 7) / 8 * 8 : n) * nsplit),
+                           dim3(64 * kTcWaves), lds(sh.Lt), st, sh, cfg0 + c, n, nsplit, (int)grouped,
+                           rec + (size_t)c * 2 * sh.Lt);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace

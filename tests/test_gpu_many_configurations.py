@@ -30,3 +30,18 @@ def test_pair_records():
         small = _plan(4, offset)
         assert np.array_equal(part, small.measure_range(0, 0, 0, 256)), offset
         small.close()
+
+
+def test_two_time_records():
+    import torch
+    print("two-time records of 2^24 configurations", flush=True)
+    plan = _plan(WORDS, 0)
+    plan.measure_time(0, 0, 64 * WORDS, copy=False)
+    rec = plan._tcws.view(torch.int64).reshape(64 * WORDS, 2, 16)
+    assert bool((rec[:, 0, 0] == 2 * 4 * 16).all())  # c[0] = R L^2 Ltau
+    ends = rec[:256].cpu().numpy(), rec[-256:].cpu().numpy()
+    plan.close()
+    for offset, part in zip((0, WORDS - 4), ends):
+        small = _plan(4, offset)
+        assert np.array_equal(part, small.measure_time(0, 0, 256)), offset
+        small.close()
