@@ -141,11 +141,11 @@ __host__ __device__ inline size_t plain_run_lds(const ShapeDev& sh) {
 
 template <bool kOne>
 __global__ void __launch_bounds__(kPlainRunThreads)
-k_plain_run(ShapeDev sh, uint32_t key0, uint32_t key1, When when, uint32_t n, Counters* ctr) {
+k_plain_run(ShapeDev sh, int cfg0, uint32_t key0, uint32_t key1, When when, uint32_t n, Counters* ctr) {
     extern __shared__ __align__(16) char lds[];  // [L2] columns, [Ltau][L2] spins
     __shared__ uint32_t tot;
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W;
-    const int cfg = blockIdx.x;  // (r*nk + w)*ns + s
+    const int cfg = cfg0 + (int)blockIdx.x;  // (r*nk + w)*ns + s
     const int s = cfg % ns, rw = cfg / ns, r = rw / nk, w = rw % nk;
     const int tid = threadIdx.x, nthr = blockDim.x;
     PlainCol* const col = (PlainCol*)lds;
@@ -217,12 +217,12 @@ k_plain_run(ShapeDev sh, uint32_t key0, uint32_t key1, When when, uint32_t n, Co
 // counts its +x, +y and +tau bonds (E = 2U - 3N).  One workgroup per
 // configuration.  After half-sweeps that took t by value it leaves the sweep
 // counter they reached on the device.
-__global__ void __launch_bounds__(1024) k_plain_energy(ShapeDev sh, Counters* ctr, uint32_t t) {
+__global__ void __launch_bounds__(1024) k_plain_energy(ShapeDev sh, int cfg0, Counters* ctr, uint32_t t) {
     __shared__ uint32_t tot;
     const int8_t* S8 = (const int8_t*)sh.S;
     const int8_t* J = (const int8_t*)sh.J;
     const int L = sh.L, L2 = sh.L2, Lt = sh.Lt, nk = sh.nk, ns = sh.W;
-    const int cfg = blockIdx.x;  // (r*nk + w)*ns + s
+    const int cfg = cfg0 + (int)blockIdx.x;  // (r*nk + w)*ns + s
     const int s = cfg % ns, rw = cfg / ns, r = rw / nk, w = rw % nk;
     const int8_t* cf = S8 + (size_t)cfg * L2 * Lt;
     const int8_t* jb = J + (size_t)s * 2 * L2;
@@ -451,8 +451,11 @@ hipError_t plain_labels_identity(const ShapeDev& sh, hipStream_t st) {
 }
 
 static hipError_t energy_and_counter(const ShapeDev& sh, Counters* ctr, uint32_t t, hipStream_t st) {
-    hipLaunchKernelGGL(k_plain_energy, dim3(sh.R * sh.nk * sh.W), dim3(std::min(1024, (sh.L2 * sh.Lt + 63) / 64 * 64)), 0, st, sh, ctr, t);
-    return hipGetLastError();
+    const int threads = std::min(1024, (sh.L2 * sh.Lt + 63) / 64 * 64);
+    return over_ranges(sh.R * sh.nk * sh.W, 1, threads, [&](int c, int n) {
+        hipLaunchKernelGGL(k_plain_energy, dim3(n), dim3(threads), 0, st, sh, c, ctr, t);
+        return hipGetLastError();
+    });
 }
 
 hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, Counters* ctr, bool from_device,
@@ -468,9 +471,11 @@ hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t 
     // against 1339; two of Ltau = 64 (2048 units) 279 against 427.
     if (plain_run_lds(sh) <= kPlainLds && (units <= 4 * kPlainRunThreads || ncfg > 8 || n == 1)) {
         const int threads = std::min(kPlainRunThreads, (units + 63) / 64 * 64);
-        hipLaunchKernelGGL(units <= threads ? k_plain_run<true> : k_plain_run<false>, dim3(sh.R * sh.nk * sh.W),
-                           dim3(threads), plain_run_lds(sh), st, sh, (uint32_t)seed, (uint32_t)(seed >> 32), when, n, store);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = over_ranges(ncfg, 1, threads, [&](int c, int m) {
+            hipLaunchKernelGGL(units <= threads ? k_plain_run<true> : k_plain_run<false>, dim3(m), dim3(threads),
+                               plain_run_lds(sh), st, sh, c, (uint32_t)seed, (uint32_t)(seed >> 32), when, n, store);
+            return hipGetLastError();
+        });
         return e == hipSuccess && from_device ? launch_advance(ctr, n, 0, st) : e;
     }
     for (uint32_t k = 0; k < n; ++k)

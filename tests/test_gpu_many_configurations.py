@@ -45,3 +45,24 @@ def test_two_time_records():
         small = _plan(4, offset)
         assert np.array_equal(part, small.measure_time(0, 0, 256)), offset
         small.close()
+
+
+def test_plain_sweeps():
+    """Configurations of 8 KB (1024 threads each); k labels have one value, U is a
+    count over the whole trajectory."""
+    print("plain sweeps of 2^22 + 64 configurations", flush=True)
+
+    def plan(samples, offset):
+        p = tfim.Plan([Shape(4, 512, samples, 1, [0.3], word_offset=offset)], 12, form=tfim.TFIM_FORM_PLAIN_I8)
+        p.init()
+        U0 = p.measure(0, tfim.TFIM_MEASURE_ENERGY)
+        p.sweep(2)
+        U = p.measure(0, tfim.TFIM_MEASURE_ENERGY)
+        p.close()
+        return U0[0, :, 0], U[0, :, 0]
+
+    n = (1 << 22) + 64
+    big = plan(n, 0)
+    for offset in (0, n // 64 - 4):
+        for got, want in zip(big, plan(256, offset)):
+            assert np.array_equal(got[64 * offset:64 * offset + 256], want), offset
