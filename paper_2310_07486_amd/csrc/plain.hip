@@ -451,8 +451,17 @@ hipError_t plain_labels_identity(const ShapeDev& sh, hipStream_t st) {
 }
 
 static hipError_t energy_and_counter(const ShapeDev& sh, Counters* ctr, uint32_t t, hipStream_t st) {
-    const int threads = std::min(1024, (sh.L2 * sh.Lt + 63) / 64 * 64);
-    return over_ranges(sh.R * sh.nk * sh.W, 1, threads, [&](int c, int n) {
+    // Wide workgroups where there are few, or where each has much to read; else
+    // their start and their additions to one counter cost more than they hide.
+    // us with 256 / 512 / 1024 threads: 64 configurations of 115200 sites 250 /
+    // 156 / 132; 1024 of 32768 231 / 217 / 212, of 4096 53 / 52 / 55, of 1024
+    // 32 / 34 / 39; 4096 of 57600 1191 / 1171 / 1176; 32768 of 1024 252 / 327 / 535.
+    const int ncfg = sh.R * sh.nk * sh.W, sites = sh.L2 * sh.Lt;
+    const int most = ncfg <= 256 || (ncfg <= 1024 && sites >= 1 << 14) ? 1024
+                     : ncfg <= 4096 && sites >= 1 << 12                ? 512
+                                                                       : 256;
+    const int threads = std::min(most, (sites + 63) / 64 * 64);
+    return over_ranges(ncfg, 1, threads, [&](int c, int n) {
         hipLaunchKernelGGL(k_plain_energy, dim3(n), dim3(threads), 0, st, sh, c, ctr, t);
         return hipGetLastError();
     });
