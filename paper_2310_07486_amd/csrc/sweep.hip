@@ -423,7 +423,7 @@ const char* sweep_variant_name(int v) {
 hipError_t launch_sweep(const ShapeDev& sh, uint64_t seed, When t, int variant, bool energy, int ncu,
                         hipStream_t st) {
     if ((variant == 0 || variant == 3) && sweep_stream_ok(sh)) {
-        const int nparts = sweep_parts(sh, energy, ncu);
+        const int nparts = sweep_parts(sh, energy, variant == 3 && sweep_helped_ok(sh), ncu);
         if (nparts > 1) return launch_sweep_parts(sh, seed, t, energy, nparts, st);
     }
     if (variant == 3 && sweep_helped_ok(sh)) return launch_sweep_helped(sh, seed, t, energy, st);
@@ -437,7 +437,7 @@ hipError_t launch_sweep(const ShapeDev& sh, uint64_t seed, When t, int variant, 
 
 hipError_t prepare_sweep(const ShapeDev& sh, int variant, bool energy, int ncu) {
     if ((variant == 0 || variant == 3) && sweep_stream_ok(sh)) {
-        const int nparts = sweep_parts(sh, energy, ncu);
+        const int nparts = sweep_parts(sh, energy, variant == 3 && sweep_helped_ok(sh), ncu);
         if (nparts > 1) return launch_sweep_parts(sh, 0, When{0, nullptr}, energy, nparts, nullptr, false);
     }
     if (variant == 3 && sweep_helped_ok(sh)) return prepare_sweep_helped(sh, energy);

@@ -1050,15 +1050,43 @@ static hipError_t launch_bc(const ShapeDev& sh, uint64_t seed, When t, hipStream
     return sh.apm ? launch_one<kE, kOcc, true>(sh, seed, t, st) : launch_one<kE, kOcc, false>(sh, seed, t, st);
 }
 
-// Parts of a configuration that fill the chip: as many workgroups as are
-// resident at once (per CU 12 waves of the kernel that counts U, 16 of the
-// other); 1 where the configurations alone take more than half of them.
-int sweep_parts(const ShapeDev& sh, bool energy, int ncu) {
-    const int slots = ncu * std::max(1, (energy ? 12 : 16) / (stream_cols(sh) / 64)), ncfg = sh.R * sh.nk * sh.W, nq = sh.Lt >> 3;
-    const int want = std::min(nq, slots / ncfg);
-    if (want < 2) return 1;
-    const int per = (nq + want - 1) / want;  // groups of 8 planes per part
-    return (nq + per - 1) / per;
+// Parts of a configuration that fill the chip (per SIMD 3 waves of the kernel that
+// counts U, 4 of the other); as many workgroups as fit at once, where that is a tenth
+// better (the waves of one start at the same SIMD, so one of 6 waves takes 2 of the
+// 3), or two waves per SIMD; 1 where the configurations alone take more than half of
+// the chip, and where the parts and their join would take longer than the whole.
+// By us per plane: 0.23 + 0.01 per wave of a configuration (0.9 of that whole, with
+// helper waves) up to 2.75 waves per SIMD (2 of workgroups of one wave), then in
+// proportion, and, lattices of one wave, no faster than 5 TB/s; the join 5 and 2e-5 per
+// site, 4e-5 with U.  Fitted to 1900 shapes of L = 2 .. 24, Ltau = 16 .. 4096 and 2 ..
+// 4096 configurations: of the 1100 that it splits, 21 take 2% or more (up to 29%)
+// longer than whole.  us per sweep, whole and parts, U counted: L = 24, Ltau = 16, 128
+// configurations 28 and 34; Ltau = 32 34 and 38; Ltau = 96 60 and 57; L = 18, Ltau = 64,
+// 128 configurations 45, in two parts 41, in four 51; not counted: L = 8, Ltau = 32, two
+// configurations 11 and 10, 512 of them 15 and 16; Ltau = 1024, 2048 of them 471 and 538.
+int sweep_parts(const ShapeDev& sh, bool energy, bool helped, int ncu) {
+    const int waves = stream_cols(sh) / 64, simd = energy ? 3 : 4, ncfg = sh.R * sh.nk * sh.W, nq = sh.Lt >> 3;
+    const int by_waves = std::max(1, 4 * simd / waves);  // workgroups per CU
+    const int fit = waves <= 4 ? by_waves : std::max(1, simd / ((waves + 3) / 4));
+    const int slots = ncu * fit;
+    const double plane = 0.23 + 0.01 * waves, free = waves == 1 ? 2.0 : 2.75;
+    const double copy = waves == 1 ? (double)ncfg * sh.Lt * sh.L2 * 16 / 5e6 : 0.0;
+    auto us = [&](int M, int blocks) {
+        const int rounds = (blocks + slots - 1) / slots;
+        const double load = (double)std::min(blocks, slots) * waves / (4 * ncu) / free;
+        return std::max(copy, rounds * M * plane * std::max(1.0, load));
+    };
+    int best = 1;
+    double least = us(sh.Lt, ncfg) * (helped ? 0.9 : 1.0);
+    for (int per_cu : {by_waves, fit, std::max(1, 8 / waves)}) {
+        const int want = std::min(nq, ncu * per_cu / ncfg);
+        if (want < 2) continue;
+        const int per = (nq + want - 1) / want;  // groups of 8 planes per part
+        const int n = (nq + per - 1) / per;
+        const double t = us(8 * per, ncfg * n) + 5 + (energy ? 4e-5 : 2e-5) * ((double)ncfg * n * sh.L2);
+        if (t * (per_cu == by_waves ? 1.0 : 1.1) < least) least = t, best = n;
+    }
+    return best;
 }
 
 template <bool kE, bool kAnti>

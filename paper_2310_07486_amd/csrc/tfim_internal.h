@@ -236,8 +236,8 @@ hipError_t launch_sweep_stream(const ShapeDev& sh, uint64_t seed, When t, bool e
 // LDS above 64 KiB), set outside any stream capture.
 hipError_t prepare_sweep(const ShapeDev& sh, int variant, bool energy, int ncu);
 // A sweep in parts along tau (nparts >= 2 from sweep_parts): the parts, then
-// the sites at their boundaries.
-int sweep_parts(const ShapeDev& sh, bool energy, int ncu);
+// the sites at their boundaries.  helped: whole, it would have helper waves.
+int sweep_parts(const ShapeDev& sh, bool energy, bool helped, int ncu);
 hipError_t launch_sweep_parts(const ShapeDev& sh, uint64_t seed, When t, bool energy, int nparts, hipStream_t st,
                               bool launch = true);
 hipError_t prepare_sweep_stream(const ShapeDev& sh, bool energy, int occ);
