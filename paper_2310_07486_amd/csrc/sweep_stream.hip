@@ -320,6 +320,36 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
     const int w = rw % nk;
     const int r = rw / nk;
 
+    // Lane masks and tables.  A part sets them up under its first loads of spins; of a
+    // whole configuration those come after them, since in flight they cost registers
+    // (variant 2 3 to 10% slower, the batched kernel 1 to 2%).
+    Tables tb;
+    auto tables = [&]() {
+        if (member)
+            for (int i = ttid; i <= nk; i += cols)
+                ml[i] = live ? sh.mask[((size_t)(r * W + j) * nk + w) * (nk + 1) + i] : 0ull;
+        if (kE && member && ttid < 64) Ublk[ttid] = 0;
+        if (kE && kDeepLds)
+            for (int i = 0; i < kDeep; ++i) DEEP[i * nthr + tid] = 0;
+        __syncthreads();
+        // entry a of the concatenated tables (u = 0, 1, 2) sits at btab[a + shift(u)]
+        const int bo0 = sh.boff[0], bo1 = sh.boff[1] - nb0, bo2 = sh.boff[2] - nb0 - nb1;
+        for (int a = tid; a < nbt; a += nthr)
+            TT[a] = (uint32_t)sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
+        if (member)
+            for (int a = ttid; a < nbt; a += cols) {
+                const uint64_t e = sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
+                const uint32_t kb = (uint32_t)(e >> 32) & 0xFFFFu, mu = (uint32_t)(e >> 48);
+                MM[2 * a] = ml[kb];
+                MM[2 * a + 1] = ml[kb + mu];
+            }
+        tb.T[0] = TT; tb.T[1] = TT + nb0; tb.T[2] = TT + nb0 + nb1;
+        tb.M[0] = MM; tb.M[1] = MM + 2 * nb0; tb.M[2] = MM + 2 * (nb0 + nb1);
+        tb.sh[0] = (uint32_t)sh.bsh[0]; tb.sh[1] = (uint32_t)sh.bsh[1]; tb.sh[2] = (uint32_t)sh.bsh[2];
+        tb.nb[0] = (uint32_t)sh.bnb[0]; tb.nb[1] = (uint32_t)sh.bnb[1]; tb.nb[2] = (uint32_t)sh.bnb[2];
+    };
+    if constexpr (!kPart) tables();
+
     const int xy = active ? ttid : 0;
     const int x = xy % L, y = xy / L;
     const int p = (x + y) & 1;
@@ -383,29 +413,7 @@ __device__ __forceinline__ void sweep_teams(const ShapeDev& sh, const int cfg0, 
     // steady state: planes A + 4, A + 5 of the next segment, already in flight
     const int voffp = voff + p * plane;
     uint64_t nn0 = ld_lane(p + 4), nn1 = ld_lane(p + 5);
-    if (member)
-        for (int i = ttid; i <= nk; i += cols)
-            ml[i] = live ? sh.mask[((size_t)(r * W + j) * nk + w) * (nk + 1) + i] : 0ull;
-    if (kE && member && ttid < 64) Ublk[ttid] = 0;
-    if (kE && kDeepLds)
-        for (int i = 0; i < kDeep; ++i) DEEP[i * nthr + tid] = 0;
-    __syncthreads();
-    // entry a of the concatenated tables (u = 0, 1, 2) sits at btab[a + shift(u)]
-    const int bo0 = sh.boff[0], bo1 = sh.boff[1] - nb0, bo2 = sh.boff[2] - nb0 - nb1;
-    for (int a = tid; a < nbt; a += nthr)
-        TT[a] = (uint32_t)sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
-    if (member)
-        for (int a = ttid; a < nbt; a += cols) {
-            const uint64_t e = sh.btab[a + (a < nb0 ? bo0 : (a < nb0 + nb1 ? bo1 : bo2))];
-            const uint32_t kb = (uint32_t)(e >> 32) & 0xFFFFu, mu = (uint32_t)(e >> 48);
-            MM[2 * a] = ml[kb];
-            MM[2 * a + 1] = ml[kb + mu];
-        }
-    Tables tb;
-    tb.T[0] = TT; tb.T[1] = TT + nb0; tb.T[2] = TT + nb0 + nb1;
-    tb.M[0] = MM; tb.M[1] = MM + 2 * nb0; tb.M[2] = MM + 2 * (nb0 + nb1);
-    tb.sh[0] = (uint32_t)sh.bsh[0]; tb.sh[1] = (uint32_t)sh.bsh[1]; tb.sh[2] = (uint32_t)sh.bsh[2];
-    tb.nb[0] = (uint32_t)sh.bnb[0]; tb.nb[1] = (uint32_t)sh.bnb[1]; tb.nb[2] = (uint32_t)sh.bnb[2];
+    if constexpr (kPart) tables();
 
     const uint32_t c3 = ctr_word3(sh.word_offset + (uint32_t)j, sh.sid, kTagMetro);
     const uint32_t c2_0 = (uint32_t)rw << 1, c2_1 = c2_0 | 1u;
