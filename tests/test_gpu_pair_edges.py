@@ -72,3 +72,47 @@ def test_pair_records_of_equal_spins(L, Lt):
         want = [Lt * Lt * L ** 3] * (2 * L) + [sign * L * L * Lt, Lt * Lt * L ** 4, Lt * Lt * L ** 8]
         assert np.array_equal(got[:, p], np.tile(np.array(want, dtype=np.int64), (64, 1)))
     plan.close()
+
+
+def _record_by_blocks(a, b, L):
+    """One row of _records for long Ltau: Q in blocks of rows (exact in float32)."""
+    row = np.zeros(2 * L + 3, dtype=np.int64)
+    H = (a @ a.T) * (b @ b.T)
+    xy = np.arange(L * L)
+    for h, c in enumerate((xy % L, xy // L)):
+        d = (c[:, None] - c[None, :]) % L
+        row[h * L:(h + 1) * L] = [H[d == k].sum() for k in range(L)]
+    fa, fb = a.astype(np.float32), b.astype(np.float32)
+    row[2 * L] = (a * b).sum()
+    for t in range(0, a.shape[1], 1024):
+        q2 = np.square((fa[:, t:t + 1024].T @ fb).astype(np.int64))
+        row[2 * L + 1] += q2.sum()
+        row[2 * L + 2] += np.square(q2).sum()
+    return row
+
+
+@pytest.mark.parametrize("Lt", [8192, 8200])  # the largest with int16 G, the first with int32
+@pytest.mark.parametrize("L", [6, 8])         # sites in slot order, in 8 x 8 blocks
+@pytest.mark.parametrize("R", [2, 5])         # two column blocks at a time, one
+def test_pair_records_of_long_lattices(L, R, Lt):
+    print(f"pair records L={L} Ltau={Lt} R={R}", flush=True)
+    sh = Shape(L, Lt, 1, R, [0.3])
+    plan = tfim.Plan([sh], 100 * L + R)
+    plan.init()
+    plan.sweep(3)
+    got = plan.measure_range(0, 0, 17, 3)
+    S = _spins(plan, sh, 18)
+    pairs = [(a, b) for a in range(R) for b in range(a + 1, R)]
+    for p in {0, len(pairs) // 2, len(pairs) - 1}:
+        a, b = pairs[p]
+        assert np.array_equal(got[1, p], _record_by_blocks(S[a], S[b], L)), (a, b)
+    # equal spins, the last replica flipped: G = Ltau, Q = +-L^2 everywhere
+    S = np.zeros((R, 1, 1, Lt, L * L), dtype=np.uint64)
+    S[R - 1] = ~np.uint64(0)
+    plan.init_spins(0, S)
+    got = plan.measure_range(0, 0, 0, 64)
+    for p, (a, b) in enumerate(pairs):
+        sign = -1 if b == R - 1 else 1
+        want = [Lt * Lt * L ** 3] * (2 * L) + [sign * L * L * Lt, Lt * Lt * L ** 4, Lt * Lt * L ** 8]
+        assert np.array_equal(got[:, p], np.tile(np.array(want, dtype=np.int64), (64, 1)))
+    plan.close()
