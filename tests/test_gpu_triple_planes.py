@@ -1,0 +1,35 @@
+"""Three-replica records on planes of every size of the blocked layout (4 x 8
+sites a block, 128 x 128 sites a tile): odd and even numbers of blocks, full and
+part tiles, three to six replicas, few configurations (the pairs of a tile on
+several workgroups) and many."""
+import numpy as np
+import pytest
+
+from oracle import measure as om
+from paper_2310_07486_amd import tfim
+from paper_2310_07486_amd.workloads import Shape, ladder
+from test_gpu_pair_edges import _spins
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(plan, sh, cfg, got):
+    G = [s @ s.T for s in _spins(plan, sh, cfg)]
+    want = [om.triple_record(G, t, sh.L) for t in om.triples(sh.n_replicas)]
+    assert np.array_equal(got, np.array(want).reshape(got.shape)), cfg
+
+
+@pytest.mark.parametrize("L,Lt,R", [(12, 72, 6), (14, 136, 4), (18, 64, 3), (20, 200, 6), (20, 16, 5), (22, 40, 4),
+                                    (24, 72, 5)])
+def test_triple_records_on_every_plane(L, Lt, R):
+    print(f"triples L={L} Ltau={Lt} R={R}", flush=True)
+    sh = Shape(L, Lt, 1, R, ladder(0.25, 0.4, 2))
+    plan = tfim.Plan([sh], 7 * L + R)
+    plan.init()
+    plan.sweep(4)
+    many = plan.measure_triples(0, 0, 128)
+    few = plan.measure_triples(0, 59, 6)
+    assert np.array_equal(few, many[59:65])
+    for cfg in (0, 63, 64, 127):
+        _check(plan, sh, cfg, many[cfg])
+    plan.close()
