@@ -21,7 +21,7 @@
 //    the 32 x 32 MFMA layout (G is symmetric), an int8 MFMA operand whose K
 //    axis runs over the sites of block kb, and the 16 carrier elements that a
 //    lane of the product needs: every access is 16 consecutive bytes per lane
-//    and 1 KB per wave.
+//    and 1 KB per wave.  (Ltau above 16312, L = 2 and 4 only: k_triple_long.)
 // 2. k_triple_mfma forms P = G'^f G'^g = 4096 h^f h^g + 64 (h^f l^g + l^f h^g)
 //    + l^f l^g with three exact int8 products on v_mfma_i32_32x32x32_i8 (the
 //    middle one with K doubled), |P| <= L^2 (Ltau/2)^2 < 2^31.  Its epilogue
@@ -301,6 +301,55 @@ k_triple_mfma(int L, int R, int ncfg, int ncopy, int psplit, int grouped, const 
     }
 }
 
+// ---------------------------------------------------------------------------
+// Ltau above kDigitLt, where G' no longer fits two digits (G = Ltau on the
+// diagonal): planes of L = 2 and 4 only, since L^2 (Ltau/2)^2 < 2^31.  A workgroup
+// per configuration, an element of the plane per thread: G^r in 32 bits in LDS,
+// every product in 64.  Bound by the latency of the rows' words.
+// ---------------------------------------------------------------------------
+constexpr int kDigitLt = 16312;  // (Ltau + 64) >> 7 <= 127, Ltau a multiple of 8
+constexpr int kLongSites = 16;
+
+__global__ void __launch_bounds__(kLongSites* kLongSites) k_triple_long(ShapeDev sh, int cfg0,
+                                                                        int64_t* __restrict__ rec) {
+    __shared__ int G[6][kLongSites * kLongSites];
+    __shared__ unsigned long long T[20 * 2 * 4];  // [NT][x, y][L]
+    const int L = sh.L, L2 = sh.L2, R = sh.R, nc = sh.nc, nxp = sh.nxp, tid = threadIdx.x;
+    const int NT = R * (R - 1) * (R - 2) / 6;
+    const bool on = tid < L2 * L2;
+    const int x = on ? tid / L2 : 0, y = on ? tid % L2 : 0;
+    const int sx = site_slot(L, x % L, x / L), sy = site_slot(L, y % L, y / L);
+    for (int r = 0; r < R; ++r) {
+        const uint64_t* const pt = sh.Pt + ((size_t)(cfg0 + (int)blockIdx.x) * R + r) * nc * nxp;
+        int n = 0;  // of opposite spins (padding bits are 0)
+#pragma unroll 8
+        for (int c = 0; c < nc; ++c) n += __popcll(pt[(size_t)c * nxp + sx] ^ pt[(size_t)c * nxp + sy]);
+        G[r][tid] = sh.Lt - 2 * n;
+    }
+    for (int e = tid; e < NT * 2 * L; e += kLongSites * kLongSites) T[e] = 0;
+    __syncthreads();
+    const int dx = bucket_of(x % L - y % L, L), dy = bucket_of(x / L - y / L, L);
+    int t = 0;
+    for (int a = 0; a < R; ++a)
+        for (int b = a + 1; b < R; ++b)
+            for (int c = b + 1; c < R; ++c, ++t) {
+                // G^e_xy (G^f G^g)_yx for the three carriers e
+                auto term = [&](int e, int f, int g) {
+                    long long p = 0;
+                    for (int z = 0; z < L2; ++z) p += (long long)G[f][y * L2 + z] * G[g][z * L2 + x];
+                    return G[e][x * L2 + y] * p;
+                };
+                const unsigned long long v = (unsigned long long)(term(a, b, c) + term(b, a, c) + term(c, a, b));
+                if (on) {
+                    atomicAdd(&T[t * 2 * L + dx], v);
+                    atomicAdd(&T[t * 2 * L + L + dy], v);
+                }
+            }
+    __syncthreads();
+    for (int e = tid; e < NT * 2 * L; e += kLongSites * kLongSites)
+        rec[(size_t)blockIdx.x * NT * 2 * L + e] = (int64_t)T[e];
+}
+
 // The records are sums of atomic adds: cleared first by a kernel (no memset
 // node, so the launch sequence may be captured in a graph).
 __global__ void k_zero_records(int64_t* __restrict__ rec, size_t n) {
@@ -313,6 +362,10 @@ hipError_t launch_triples_on(const ShapeDev& sh, int cfg0, int ncfg, int64_t* re
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     hipError_t e;
+    if (sh.Lt > kDigitLt) {
+        hipLaunchKernelGGL(k_triple_long, dim3((unsigned)ncfg), dim3(kLongSites * kLongSites), 0, st, sh, cfg0, rec);
+        return hipGetLastError();
+    }
     const int NT = sh.R * (sh.R - 1) * (sh.R - 2) / 6;
     const size_t nrec = (size_t)ncfg * NT * 2 * sh.L;
     hipLaunchKernelGGL(k_zero_records, dim3((unsigned)std::min<size_t>((nrec + 255) / 256, 1024)), dim3(256), 0,

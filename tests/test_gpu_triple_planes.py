@@ -1,7 +1,9 @@
 """Three-replica records on planes of every size of the blocked layout (4 x 8
 sites a block, 128 x 128 sites a tile): odd and even numbers of blocks, full and
 part tiles, three to six replicas, few configurations (the pairs of a tile on
-several workgroups) and many."""
+several workgroups) and many; and at the largest Ltau of the two-digit
+products, the first beyond it and the largest that a shape may have, where the
+records of equal spins are known in closed form."""
 import numpy as np
 import pytest
 
@@ -32,4 +34,22 @@ def test_triple_records_on_every_plane(L, Lt, R):
     assert np.array_equal(few, many[59:65])
     for cfg in (0, 63, 64, 127):
         _check(plan, sh, cfg, many[cfg])
+    plan.close()
+
+
+@pytest.mark.parametrize("L,Lt,R", [(2, 16312, 3), (2, 16320, 6), (2, 46336, 4), (4, 16312, 6), (4, 16320, 3),
+                                    (4, 23168, 5)])
+def test_triple_records_of_long_lattices(L, Lt, R):
+    print(f"triples L={L} Ltau={Lt} R={R}", flush=True)
+    sh = Shape(L, Lt, 1, R, [0.3])
+    plan = tfim.Plan([sh], 7 * L + R)
+    plan.init()
+    plan.sweep(2)
+    got = plan.measure_triples(0, 5, 40)
+    for cfg in (5, 44):
+        _check(plan, sh, cfg, got[cfg - 5])
+    S = np.zeros((R, 1, 1, Lt, L * L), dtype=np.uint64)
+    S[0] = ~np.uint64(0)  # replica 0 flipped: the same G
+    plan.init_spins(0, S)
+    assert np.all(plan.measure_triples(0, 0, 64) == 3 * L ** 5 * Lt ** 3)
     plan.close()
