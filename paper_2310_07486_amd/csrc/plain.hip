@@ -467,18 +467,34 @@ static hipError_t energy_and_counter(const ShapeDev& sh, Counters* ctr, uint32_t
     });
 }
 
+// A workgroup per configuration, unless a run of several sweeps goes over
+// few large ones.  20 sweeps and a read-back at L = 16, Ltau = 216 (6912
+// units): two configurations 710 us against 505 over the whole chip, but 64
+// of them 949 against 1694, and two with tempering at every sweep 1222
+// against 1339; two of Ltau = 64 (2048 units) 279 against 427.
+static bool plain_in_lds(const ShapeDev& sh, uint32_t n) {
+    return plain_run_lds(sh) <= kPlainLds &&
+           (sh.L2 * ((sh.Lt + 7) / 8) <= 4 * kPlainRunThreads || sh.R * sh.nk * sh.W > 8 || n == 1);
+}
+
+// About 50 ms, by what a sweep in LDS takes: 5 us per unit of a thread (2 with one),
+// over the full chip 1.6e-5 us per unit (220 for 2048 configurations of 6912).  Runs of
+// 20 ms lost 1% to their ends there, of 5 ms 4%.
+uint32_t plain_run_limit(const ShapeDev& sh) {
+    constexpr uint32_t kMost = 1u << 12;
+    if (!plain_in_lds(sh, 2)) return kMost;  // launches of half a sweep each
+    const int units = sh.L2 * ((sh.Lt + 7) / 8), per = (units + kPlainRunThreads - 1) / kPlainRunThreads;
+    const double us = std::max(5.0 * per, 1.6e-5 * units * ((double)sh.R * sh.nk * sh.W));
+    return (uint32_t)std::min<double>(kMost, std::max(1.0, 5e4 / us));
+}
+
 hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, Counters* ctr, bool from_device,
                         hipStream_t st) {
     const When when{t, from_device ? ctr : nullptr};
     Counters* const store = from_device ? nullptr : ctr;
     const size_t total = (size_t)sh.R * sh.nk * sh.W * sh.L2 * ((sh.Lt + 7) / 8);
     const int units = sh.L2 * ((sh.Lt + 7) / 8), ncfg = sh.R * sh.nk * sh.W;
-    // A workgroup per configuration, unless a run of several sweeps goes over
-    // few large ones.  20 sweeps and a read-back at L = 16, Ltau = 216 (6912
-    // units): two configurations 710 us against 505 over the whole chip, but 64
-    // of them 949 against 1694, and two with tempering at every sweep 1222
-    // against 1339; two of Ltau = 64 (2048 units) 279 against 427.
-    if (plain_run_lds(sh) <= kPlainLds && (units <= 4 * kPlainRunThreads || ncfg > 8 || n == 1)) {
+    if (plain_in_lds(sh, n)) {
         const int threads = std::min(kPlainRunThreads, (units + 63) / 64 * 64);
         const hipError_t e = over_ranges(ncfg, 1, threads, [&](int c, int m) {
             hipLaunchKernelGGL(units <= threads ? k_plain_run<true> : k_plain_run<false>, dim3(m), dim3(threads),

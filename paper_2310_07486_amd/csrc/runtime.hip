@@ -651,8 +651,7 @@ static hipError_t enqueue_plain(tfim_plan* pl, uint64_t n) {
     for (size_t i = 0; i < pl->shapes.size() && e == hipSuccess; ++i) {
         const uint64_t pe = pl->shapes[i].s.pt_every, end = pl->t[i] + n;
         while (pl->t[i] < end && e == hipSuccess) {
-            // at most 2^12 sweeps in a launch (tens of ms)
-            uint64_t run = std::min<uint64_t>(end - pl->t[i], 1u << 12);
+            uint64_t run = std::min<uint64_t>(end - pl->t[i], tfim::plain_run_limit(dev_of(pl, (int)i)));
             if (pe > 0) run = std::min(run, pe - pl->t[i] % pe);
             std::pair<hipEvent_t, hipEvent_t> ev;
             e = timing_begin(pl, ev);

@@ -321,6 +321,7 @@ hipError_t plain_energy(const ShapeDev& sh, hipStream_t st);
 // n >= 1 sweeps t, t + 1, .. and the energy recount after the last; one tempering
 // step m.  from_device: t, m are read from ctr and ctr is advanced by a launch of
 // its own; else they go by value and the last kernel stores what follows in ctr.
+uint32_t plain_run_limit(const ShapeDev& sh);  // sweeps that one call may take
 hipError_t plain_sweeps(const ShapeDev& sh, uint64_t seed, uint32_t t, uint32_t n, Counters* ctr, bool from_device,
                         hipStream_t st);
 hipError_t plain_temper(const ShapeDev& sh, uint64_t seed, uint32_t m, Counters* ctr, bool from_device,

@@ -80,3 +80,19 @@ def test_callers_graph_goes_on(L, Lt, ns, nk, pt):
             assert all(np.array_equal(a, b) for a, b in zip(plan.get_state(i), ref.get_state(i)))
         plan.close()
         ref.close()
+
+
+def test_a_long_call_in_several_runs():
+    """Runs are cut at 4096 sweeps, or where they would take about 50 ms: 2048
+    configurations of 6912 units at 220 sweeps."""
+    _say("plain: calls longer than a run")
+    for L, Lt, ns, nk, n in ((2, 8, 2, 1, 9000), (16, 216, 128, 8, 450)):
+        got = []
+        for parts in (1, 10):
+            plan = tfim.Plan([Shape(L, Lt, ns, 2, ladder(0.22, 0.3, nk), pt_every=0)], 4, form=PLAIN)
+            plan.init()
+            for _ in range(parts):
+                plan.sweep(n // parts)
+            got.append([plan.export_spins(0), *plan.get_state(0), np.array(plan.counters())])
+            plan.close()
+        assert all(np.array_equal(a, b) for a, b in zip(*got))
