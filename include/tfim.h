@@ -187,7 +187,8 @@ tfim_status tfim_measure(tfim_plan *plan, uint32_t shape, uint32_t what, void *h
  * mode 1: plain per-sample form (one launch per configuration, one matrix
  * element per thread, int32 multiply-accumulate, no MFMA).  flags:
  * TFIM_MEASURE_REUSE_LAYOUT skips the bit transposition (valid only if the
- * state did not change since the last measurement of this shape).
+ * state did not change since the last measurement of this shape: a sweep may
+ * use the layout's memory for its own sums).
  * out == NULL: enqueue only (asynchronous, for timing); otherwise the call
  * synchronises and copies the records.  ncfg = 0 measures nothing (the bit
  * layout is still refreshed unless TFIM_MEASURE_REUSE_LAYOUT); a range
@@ -350,8 +351,15 @@ tfim_status tfim_set_state(tfim_plan *plan, uint32_t shape, const void *S_host,
 /* Launch schedules of tfim_sweep (both give bit-identical spins, labels,
  * energies and counters).
  * TFIM_SCHED_PER_SHAPE (default): per sweep, one sweep-kernel launch per
- *   shape (one workgroup per configuration), then per shape a tempering
- *   launch when due and the counter advance: the plain form.
+ *   shape, a workgroup per configuration (where there are few, a workgroup
+ *   per part of one along tau, and a second launch for the sites between the
+ *   parts), then per shape a tempering launch when due.  The sweep and
+ *   tempering counters go to the kernels by value and to the device at the
+ *   end of the call; calls that the caller captures in a graph of its own,
+ *   and every later one of that plan, read and advance the device's, so that
+ *   each replay does the next sweeps.  A plain-form plan runs several sweeps
+ *   of one shape in a launch, up to the next tempering step, where a
+ *   configuration fits in LDS, and half a sweep per launch otherwise.
  * TFIM_SCHED_BATCHED: per sweep, ONE launch of a persistent kernel for all
  *   shapes.  Its workgroups take work items (shape, run of configurations)
  *   from a device queue in longest-first order, and pack several
@@ -410,7 +418,8 @@ tfim_status tfim_autotune(tfim_plan *plan, uint32_t sweeps_per_trial, const char
 tfim_status tfim_get_tuning(const tfim_plan *plan, tfim_tuning *out);
 
 /* Sweep kernel variant of the per-shape schedule (all give bit-identical
- * chains): 0 = streaming (one barrier per two tau planes), 1 = chunked
+ * chains; 0 and 3 sweep few configurations in parts along tau): 0 =
+ * streaming (one barrier per two tau planes), 1 = chunked
  * (eight tau planes per step), 2 = streaming compiled for at least five
  * waves per SIMD, 3 (default) = streaming with three helper waves that
  * compute the uniforms and lane masks of the three column waves sharing a
@@ -418,12 +427,13 @@ tfim_status tfim_get_tuning(const tfim_plan *plan, tfim_tuning *out);
 tfim_status tfim_set_variant(tfim_plan *plan, uint32_t variant);
 
 /* Kernel timing: while enabled, tfim_sweep records a pair of HIP events on
- * the bound stream around every sweep-kernel launch (per-shape schedule:
- * one launch per shape and sweep) or around every graph replay (batched
- * schedule: the span covers the sweeps, tempering and counter advances of
- * the replay, and counts as that many launches).  tfim_get_timing
- * synchronises the stream, returns the summed time in ms and the number of
- * timed launches since the last call, and resets them. */
+ * the bound stream around the launches of every shape and sweep (per-shape
+ * schedule), around a run of sweeps of a shape (plain form: the span covers
+ * the run and its energy count) or around every graph replay (batched and
+ * concurrent schedules: the span covers the sweeps, tempering and counter
+ * advances of the replay).  tfim_get_timing synchronises the stream, returns
+ * the summed time in ms and the number of timed sweeps of a shape (of the plan,
+ * for replays) since the last call, and resets them. */
 tfim_status tfim_set_timing(tfim_plan *plan, uint32_t enable);
 tfim_status tfim_get_timing(tfim_plan *plan, double *kernel_ms, uint64_t *launches);
 

