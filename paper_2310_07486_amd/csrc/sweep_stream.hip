@@ -1059,10 +1059,10 @@ static hipError_t launch_bc(const ShapeDev& sh, uint64_t seed, When t, hipStream
 }
 
 // Parts of a configuration that fill the chip (per SIMD 3 waves of the kernel that
-// counts U, 4 of the other); as many workgroups as fit at once, where that is a tenth
-// better (the waves of one start at the same SIMD, so one of 6 waves takes 2 of the
-// 3), or two waves per SIMD; 1 where the configurations alone take more than half of
-// the chip, and where the parts and their join would take longer than the whole.
+// counts U, 4 of the other); or as many workgroups as fit at once (the waves of one
+// start at the same SIMD, so one of 6 waves takes 2 of the 3); or two waves per SIMD,
+// where that is a tenth better; 1 where the configurations alone take more than half
+// of the chip, and where the parts and their join would take longer than the whole.
 // By us per plane: 0.23 + 0.01 per wave of a configuration (0.9 of that whole, with
 // helper waves) up to 2.75 waves per SIMD (2 of workgroups of one wave), then in
 // proportion, and, lattices of one wave, no faster than 5 TB/s; the join 5 and 2e-5 per
@@ -1086,14 +1086,17 @@ int sweep_parts(const ShapeDev& sh, bool energy, bool helped, int ncu) {
     };
     int best = 1;
     double least = us(sh.Lt, ncfg) * (helped ? 0.9 : 1.0);
-    for (int per_cu : {by_waves, fit, std::max(1, 8 / waves)}) {
+    auto consider = [&](int per_cu, double handicap) {
         const int want = std::min(nq, ncu * per_cu / ncfg);
-        if (want < 2) continue;
+        if (want < 2) return;
         const int per = (nq + want - 1) / want;  // groups of 8 planes per part
         const int n = (nq + per - 1) / per;
         const double t = us(8 * per, ncfg * n) + 5 + (energy ? 4e-5 : 2e-5) * ((double)ncfg * n * sh.L2);
-        if (t * (per_cu == by_waves ? 1.0 : 1.1) < least) least = t, best = n;
-    }
+        if (t * handicap < least) least = t, best = n;
+    };
+    consider(by_waves, 1.0);
+    consider(fit, 1.0);
+    consider(std::max(1, 8 / waves), 1.1);
     return best;
 }
 

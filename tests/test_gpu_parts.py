@@ -100,3 +100,25 @@ def test_callers_graph_goes_on():
             assert np.array_equal(plan.export_spins(i), ref.export_spins(i))
         plan.close()
         ref.close()
+
+
+@pytest.mark.parametrize("L,Lt,W,R,nk,pt", [
+    (18, 256, 1, 4, 32, 1),   # six waves a workgroup: as many as fit, two parts
+    (18, 1024, 1, 4, 24, 1),  # the same in two rounds of workgroups, five parts
+    (4, 128, 4, 4, 64, 1),    # one wave: two to a SIMD, two parts
+    (4, 128, 4, 4, 64, 0),    # four parts, two where U is counted
+    (24, 16, 1, 2, 64, 1),    # whole: the join would cost more
+    (8, 64, 8, 4, 60, 0),     # whole: two waves per SIMD already
+])
+def test_every_choice_of_parts(L, Lt, W, R, nk, pt):
+    print(f"choice of parts L={L} Ltau={Lt} W={W} R={R} nk={nk} pt={pt}", flush=True)
+    sh = Shape(L, Lt, W, R, ladder(0.2, 0.4, nk), pt_every=pt)
+    got = []
+    for variant in (3, 1):
+        plan = tfim.Plan([sh], L + Lt)
+        plan.set_variant(variant)
+        plan.init()
+        plan.sweep(3)
+        got.append(_state(plan))
+        plan.close()
+    assert _same(*got)
